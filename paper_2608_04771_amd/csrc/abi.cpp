@@ -143,10 +143,10 @@ reco_status_t reco_score(const reco_kv_cache_t *cache, int32_t layer0, int32_t n
   if (st != RECO_OK) return st;
   if (static_cast<int64_t>(G) * w > reco::kScoreMaxRows) return RECO_ERR_UNSUPPORTED;
   if (cache->capacity > kMaxScoreCapacity) return RECO_ERR_UNSUPPORTED;
-  const size_t need = reco_score_workspace_size(cache, n_layers, n_q_heads, w);
+  const int units = n_layers * cache->batch * cache->n_kv_heads;
+  const size_t need = reco::score_min_workspace_bytes(units, cache->capacity, G * w);
   if (!ws || ws_bytes < need) return RECO_ERR_WORKSPACE;
 
-  const int units = n_layers * cache->batch * cache->n_kv_heads;
   reco::ScoreParams p{};
   p.k = cache->k;
   p.len = cache->len;
@@ -154,11 +154,9 @@ reco_status_t reco_score(const reco_kv_cache_t *cache, int32_t layer0, int32_t n
   p.scores = scores;
   p.rows = G * w;
   p.rows_pad = (p.rows + 15) / 16 * 16;
-  p.chunks = (cache->capacity + reco::kScoreChunk - 1) / reco::kScoreChunk;
-  p.chunk_keys = reco::kScoreChunk;
   p.cus = current_compute_units();
   p.row_part = reinterpret_cast<float *>(ws);
-  p.row_stat = p.row_part + static_cast<size_t>(units) * p.chunks * p.rows_pad * 2;
+  p.part_slots = static_cast<int64_t>(ws_bytes / (static_cast<size_t>(p.rows_pad) * 2 * sizeof(float)));
   p.given = row_stats;
   p.dev_err = dev_err;
   p.layer0 = layer0;
@@ -166,8 +164,6 @@ reco_status_t reco_score(const reco_kv_cache_t *cache, int32_t layer0, int32_t n
   p.batch = cache->batch;
   p.hkv = cache->n_kv_heads;
   p.cap = cache->capacity;
-  p.group = G;
-  p.hq = n_q_heads;
   p.w = w;
   p.causal = (flags & RECO_SCORE_CAUSAL) ? 1 : 0;
   p.scale_log2 = scale * 1.4426950408889634f;

@@ -17,19 +17,23 @@ struct ScoreParams {
   const int32_t *len;
   const void *q_win;      // [n_layers][batch][hq][w][D]
   float *scores;          // [n_layers][batch][hkv][cap]
-  float *row_part;        // [units][chunks][rows_pad][2]  per-chunk (max, sum) in log2 domain
-  float *row_stat;        // [units][rows_pad][2]          (max, 1/sum)
+  float *row_part;        // [part_slots][rows_pad][2]  (max, sum) of a workgroup's segment, log2 domain
   const float *given;     // nullable [n_layers][batch][hq][w][2] window-row (max, sum) from decode
   int32_t *dev_err;
-  int layer0, n_layers, batch, hkv, cap, group, hq, w, rows, rows_pad, chunks;
-  int chunk_keys;         // keys per work item (set by launch_score; chunks = ceil(cap / chunk_keys))
+  int64_t part_slots;     // partials the workspace holds (a call writes at most grid + units - 1)
+  int layer0, n_layers, batch, hkv, cap, w, rows, rows_pad;
+  int chunk_keys;         // keys per work item (set by launch_score)
   int cus;                // compute units of the device (persistent grids)
   int causal;
   float scale_log2;
 };
-constexpr int kScoreChunk = 512;      // keys per workgroup of the row-split kernels (workspace sizing)
+constexpr int kScoreChunk = 512;      // most keys per work item
+constexpr int kScoreMaxGrid = 256;    // workgroups the preferred workspace is sized for
 constexpr int kScoreMaxRows = 4096;   // G * w limit
+// The size a caller is told, and the least a call takes: with less than the
+// former a small call runs on fewer workgroups.
 size_t score_workspace_bytes(int units, int capacity, int rows);
+size_t score_min_workspace_bytes(int units, int capacity, int rows);
 hipError_t launch_score(const ScoreParams &p, int dtype, int head_dim, hipStream_t s);
 
 // ---- selection + in-place compaction ----------------------------------------

@@ -5,31 +5,44 @@
 // query of head h*G + g at absolute position pos = L - w + t.  Scoring takes
 // the softmax normaliser (max, sum) of every window row (a statistics pass
 // over K, or the values decode wrote for the window tokens), then the mass
-// pass adds exp2(x - max) / sum over all rows of each key.  Logits come from
-// the matrix cores (16 keys x 16 rows per v_mfma_f32_16x16x32_bf16, bf16
-// products accumulated in fp32).
+// pass adds exp2(x - max) / sum over all rows of each key.
 //
-// Two kernel families:
-// * key-split (most shapes): a persistent grid of one eight-wave workgroup
-//   per CU.  A workgroup stages the unit's window rows in LDS once per
-//   segment of its share of the keys, and every wave walks its own groups of
-//   64 keys, loading their K fragments from global memory straight into
-//   registers and multiplying them against every row tile read from LDS;
-//   each score is summed in registers and written once, and no barrier runs
-//   inside the key loop.
-// * row-split (window rows that do not fit the LDS of a CU next to the
-//   per-wave state, and fp32 at head_dim 128): per (unit, 512-key chunk)
-//   four waves split the window rows, held as MFMA fragments in registers,
-//   and stream the chunk's keys through a double-buffered LDS stage; a row
-//   merge kernel combines the per-chunk statistics.
+// Both passes are a persistent grid of one eight-wave workgroup (two waves
+// per SIMD) per CU.  A workgroup takes an equal share of all units' keys and
+// walks it as segments, the pieces inside one unit: it stages the unit's
+// window rows in LDS once per segment (in blocks of at most max_rows), and
+// every wave then walks its own groups of 32 * KT keys, the group's K
+// fragments loaded from global memory straight into registers, with no
+// barrier in the loop.
 //
-// Measured on the gfx950 issue model: a 16x16x32 bf16 MFMA occupies a SIMD
-// for 16 cycles and hides only about 5 cycles of exp or 8-11 of FMA issue
-// from its own wave (3-8 from the other wave of the SIMD), v_exp_f32 takes
-// about 8 cycles and an FMA 4 (2 with two waves per SIMD).  Each (row, key) pair
-// needs a quarter of an MFMA plus one exp2 and two FMA-class operations per
-// pass, so the passes are bound by MFMA + VALU issue combined, not by either
-// alone; both families keep the per-pair work at that minimum.
+// A tile is 32 keys x 32 window rows, S^T = K.Q^T, on the 32x32 MFMAs: a lane
+// holds 16 keys of one window row, so a row's (max, sum) is one register per
+// lane.  Measured on the box (in-bounds probes, two waves per SIMD): a
+// 32x32x16 bf16 MFMA occupies the matrix core for 32 cycles and takes no
+// issue cycles from the other wave's VALU work, where a 16x16x32 one takes
+// about 4 of its 16; FMA and add take 4 cycles and v_exp_f32 8.  A pair
+// (row, key) needs one FMA, one exp2 and one add, so 64 pairs cost 16 cycles
+// of VALU and, at head_dim 128, 16 cycles of matrix core: the two pipes are
+// balanced, and a pass can reach half the time of doing them in turn only if
+// they overlap.  So the tiles are software-pipelined inside each wave: the
+// products of the next tile are issued between the exponentials of the
+// current one, through two accumulators, and each Q fragment register is
+// reloaded from LDS right after its last use.  In a loop of its own the pair
+// of waves then takes 750 cycles per 64 keys x 32 rows and wave, against 512
+// with perfect overlap: an MFMA takes about 10 cycles of its SIMD's issue.
+//
+// Measured (both sides on one box): 28 layers x 4 heads x 16,384 keys, 448
+// rows, two passes: 442 us, after 534 us with 16x16x32 tiles in turn with
+// their exponentials and a row-merge kernel between the passes.  Under that
+// load the card lowers its clock (1.4 GHz against 2.1 GHz in short runs), so
+// it is the energy of the products that bounds the call, and variants with
+// fewer stalls measure the same.  64 units of 65,536 keys, 160 rows, one pass:
+// 247 us (4.4 TB/s of K) after 255 us.  Two fp32 units of 2,048 keys: 27 us
+// after 98 us (their keys and row tiles spread over 66 CUs instead of 8).
+// Slower: the next group's K fragments held in registers a group ahead (they
+// spill: 309 us for the 64 units, where reloading each fragment after its last
+// use takes 245 us), and touching the next group's lines a group ahead (275 us:
+// the fragments' 16-byte accesses keep the address unit busy half of the time).
 #include "reco_device.hpp"
 #include "reco_kernels.hpp"
 
@@ -39,1029 +52,813 @@ namespace reco {
 
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kWaves = 4;       // waves per scoring workgroup
-constexpr int kBlock = 32;        // keys per LDS block (two 16-key MFMA tiles)
+constexpr int kWaves = 8;
+constexpr int kThreads = kWaves * kWave;
+constexpr int kTileRows = 32;
 
-// Sum over the four lanes {l, l^16, l^32, l^48} without an LDS round trip:
-// gfx950's row swaps hand each lane its partner row's value (rows 0/1 and
-// 2/3 for the 16-lane swap, 0/2 and 1/3 for the 32-lane swap), so two
-// butterfly steps leave the group's total in every lane.  Each step adds the
-// same two values as a shuffle-based butterfly, so the result is the same.
-__device__ __forceinline__ float group4_sum_swap(float v) {
-  const auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(r16[0]) + __uint_as_float(r16[1]);
-  const auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
-}
-
-struct UnitInfo {
-  int lc, b, h;
-  size_t cunit;   // unit index in the whole cache
-  size_t ounit;   // unit index among the covered layers
-  int L;
-};
-
-__device__ __forceinline__ UnitInfo unit_info(const ScoreParams &p, int unit) {
-  UnitInfo u;
-  const int per_layer = p.batch * p.hkv;
-  u.lc = unit / per_layer;
-  u.b = (unit % per_layer) / p.hkv;
-  u.h = unit % p.hkv;
-  u.cunit = (static_cast<size_t>(p.layer0 + u.lc) * p.batch + u.b) * p.hkv + u.h;
-  u.ounit = static_cast<size_t>(unit);
-  int L = p.len[u.cunit];
-  u.L = L < 0 ? 0 : (L > p.cap ? p.cap : L);
-  return u;
-}
-
-// Workgroup -> (chunk, unit) for the statistics and mass passes.  The
-// dispatcher hands consecutive workgroup ids to the eight XCDs in turn, and
-// every XCD has its own L2; ids are laid out so that all chunks of a unit
-// share one id residue mod 8 (one XCD), so each unit's window queries, which
-// every chunk of the unit reads, come from HBM once instead of once per XCD.
-// The grid is (8 x chunks, units / 8 rounded up): workgroup (x, y) has id
-// y * 8 * chunks + x, so id mod 8 = x mod 8; it takes unit 8y + x mod 8 and
-// chunk x / 8.  Padding workgroups (unit past the last) return at once.
-__device__ __forceinline__ bool xcd_chunk_unit(const ScoreParams &p, int &chunk, int &unit) {
-  unit = static_cast<int>(blockIdx.y) * 8 + static_cast<int>(blockIdx.x & 7);
-  chunk = static_cast<int>(blockIdx.x >> 3);
-  return unit < p.n_layers * p.batch * p.hkv;
-}
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 template <typename T, int D>
 struct ScoreCfg {
-  using MF = Mfma<T>;
-  static constexpr int dq = D / 4;                       // head-dim elements per lane group
-  static constexpr int steps = dq / MF::kPerLane;        // MFMAs per 16x16 logit tile
   static constexpr int row_bytes = D * (int)sizeof(T);
-  static constexpr int k_stride = row_bytes + 16;        // padded, 16-byte aligned LDS pitch
-  static constexpr int stage_bytes = kBlock * k_stride;
-  static constexpr int lanes_per_row = row_bytes / 16;
-  static constexpr int pieces = kBlock * lanes_per_row;              // 16-byte pieces per block
-  static constexpr int max_loads = pieces / (kWaves * kWave);        // per thread (4-wave workgroups)
-};
-
-template <typename T, int D, int RTW>
-struct RowBlock {
-  using MF = Mfma<T>;
-  using frag = typename MF::frag;
-  static constexpr int steps = ScoreCfg<T, D>::steps;
-  frag q[RTW][steps];
-  int pos[RTW];      // absolute position of the lane's row (for causality)
-  bool valid[RTW];   // the lane's row exists
-
-  // Rows of tiles tile0 + k (k < RTW) for lane (col, grp).
-  __device__ __forceinline__ void load(const ScoreParams &p, const UnitInfo &u, int tile0, int col, int grp) {
-#pragma unroll
-    for (int k = 0; k < RTW; ++k) {
-      const int r = (tile0 + k) * 16 + col;
-      const int g = r / p.w;
-      const int t = r - g * p.w;
-      const int ps = u.L - p.w + t;
-      valid[k] = (r < p.rows) && (ps >= 0);
-      pos[k] = ps;
-      const T *qrow = reinterpret_cast<const T *>(p.q_win) +
-                      (((static_cast<size_t>(u.lc) * p.batch + u.b) * p.hq + u.h * p.group + (valid[k] ? g : 0)) * p.w +
-                       (valid[k] ? t : 0)) * D + grp * ScoreCfg<T, D>::dq;
-#pragma unroll
-      for (int c = 0; c < steps; ++c)
-        q[k][c] = valid[k] ? load_frag(qrow + c * MF::kPerLane) : zero_frag(frag{});
-    }
-  }
-};
-
-// The thread's 16-byte pieces of one 32-key block of K (piece i * 256 + thread).
-template <typename T, int D>
-struct BlockRegs {
-  uint4 r[ScoreCfg<T, D>::max_loads];
-};
-
-// Global -> registers: the thread's pieces of the 32-key block at kb (rows
-// past the end of the cache read row 0 and are masked later).
-template <typename T, int D>
-__device__ __forceinline__ void load_block(BlockRegs<T, D> &regs, const T *kbase, int kb, int L) {
-  using Cfg = ScoreCfg<T, D>;
-#pragma unroll
-  for (int i = 0; i < Cfg::max_loads; ++i) {
-    const int piece = i * kThreads + static_cast<int>(threadIdx.x);
-    const int r = piece / Cfg::lanes_per_row;
-    const int key = kb + r;
-    const unsigned char *src =
-        reinterpret_cast<const unsigned char *>(kbase + static_cast<size_t>(key < L ? key : 0) * D);
-    regs.r[i] = nt_load_u4(src + (piece % Cfg::lanes_per_row) * 16);
-  }
-}
-
-template <typename T, int D>
-__device__ __forceinline__ void store_block(unsigned char *stage, const BlockRegs<T, D> &regs) {
-  using Cfg = ScoreCfg<T, D>;
-#pragma unroll
-  for (int i = 0; i < Cfg::max_loads; ++i) {
-    const int piece = i * kThreads + static_cast<int>(threadIdx.x);
-    const int r = piece / Cfg::lanes_per_row;
-    *reinterpret_cast<uint4 *>(stage + r * Cfg::k_stride + (piece % Cfg::lanes_per_row) * 16) = regs.r[i];
-  }
-}
-
-// MFMA operand of 16-key tile kt of the staged block: lane holds key
-// kt*16 + col, head-dim slice grp*dq + c*kpl.
-template <typename T, int D>
-__device__ __forceinline__ void key_frags(const unsigned char *stage, int kt, int col, int grp,
-                                          typename Mfma<T>::frag (&kf)[ScoreCfg<T, D>::steps]) {
-  using Cfg = ScoreCfg<T, D>;
-  const T *row = reinterpret_cast<const T *>(stage + (kt * 16 + col) * Cfg::k_stride) + grp * Cfg::dq;
-#pragma unroll
-  for (int c = 0; c < Cfg::steps; ++c) kf[c] = load_frag(row + c * Mfma<T>::kPerLane);
-}
-
-// Statistics pass body for one 32-key block (two 16-key tiles): S^T = K.Q^T,
-// lane holds keys kb + kt*16 + 4*grp + i of row (tile0 + k)*16 + col; online
-// (max, sum) per lane over its 8 keys of the block at once (one rescale per
-// block), merged over the lane groups at the end of the chunk.  With a
-// positive scale the maximum is taken on the raw products and each term is
-// one fused multiply-add into the exponent.
-template <typename T, int D, int RTW, bool FULL>
-__device__ __forceinline__ void stats_block(const ScoreParams &p, const UnitInfo &u, const RowBlock<T, D, RTW> &rb,
-                                            const unsigned char *stage, int kb, int col, int grp,
-                                            float (&m)[RTW], float (&z)[RTW]) {
-  using MF = Mfma<T>;
-  using Cfg = ScoreCfg<T, D>;
-  typename MF::frag kf[2][Cfg::steps];
-#pragma unroll
-  for (int kt = 0; kt < 2; ++kt) key_frags<T, D>(stage, kt, col, grp, kf[kt]);
-  const float c = p.scale_log2;
-#pragma unroll
-  for (int k = 0; k < RTW; ++k) {
-    f32x4_t s[2];
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-      s[kt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int st = 0; st < Cfg::steps; ++st) s[kt] = MF::mma(kf[kt][st], rb.q[k][st], s[kt]);
-    }
-    float v[8];
-    bool vis[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      v[e] = s[e >> 2][e & 3];
-      if constexpr (FULL) {
-        vis[e] = true;
-      } else {
-        const int key = kb + (e >> 2) * 16 + 4 * grp + (e & 3);
-        vis[e] = key < u.L && (!p.causal || key <= rb.pos[k]);
-      }
-    }
-    if (c > 0.f) {
-      float vmax = -INFINITY;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) vmax = fmaxf(vmax, vis[e] ? v[e] : -INFINITY);
-      const float mn = fmaxf(m[k], vmax * c);
-      if (FULL || mn != -INFINITY) {
-        float sum = z[k] * fast_exp2(m[k] - mn);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) sum += vis[e] ? fast_exp2(fmaf(v[e], c, -mn)) : 0.f;
-        z[k] = sum;
-        m[k] = mn;
-      }
-    } else {
-      float x[8];
-      float tmax = -INFINITY;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        x[e] = vis[e] ? v[e] * c : -INFINITY;
-        tmax = fmaxf(tmax, x[e]);
-      }
-      const float mn = fmaxf(m[k], tmax);
-      if (FULL || mn != -INFINITY) {
-        float sum = z[k] * fast_exp2(m[k] - mn);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) sum += fast_exp2(x[e] - mn);
-        z[k] = sum;
-        m[k] = mn;
-      }
-    }
-  }
-}
-
-template <typename T, int D, int RTW>
-__global__ __launch_bounds__(kThreads, 2) void score_stats_kernel(ScoreParams p) {
-  constexpr int n_waves = kWaves;
-  using Cfg = ScoreCfg<T, D>;
-  using RB = RowBlock<T, D, RTW>;
-  __shared__ __attribute__((aligned(16))) unsigned char stage[2][Cfg::stage_bytes];
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
-  const int col = lane & 15, grp = lane >> 4;
-  int chunk, unit;
-  if (!xcd_chunk_unit(p, chunk, unit)) return;
-  const UnitInfo u = unit_info(p, unit);
-  const int k0 = chunk * kScoreChunk;
-  if (k0 >= u.L) return;
-  const int k1 = min(u.L, k0 + kScoreChunk);
-  const T *kbase = reinterpret_cast<const T *>(p.k) + u.cunit * p.cap * D;
-  const int row_tiles = p.rows_pad / 16;
-  // Keys every valid window row sees: below L, and (causal) up to L - w.
-  const int full_end = p.causal ? min(u.L, u.L - p.w + 1) : u.L;
-
-  for (int tg = 0; tg < row_tiles; tg += n_waves * RTW) {
-    const int tile0 = tg + wave * RTW;   // tiles past row_tiles hold zero queries; never stored
-    RB rb;
-    rb.load(p, u, tile0, col, grp);
-    float m[RTW], z[RTW];
-#pragma unroll
-    for (int k = 0; k < RTW; ++k) {
-      m[k] = -INFINITY;
-      z[k] = 0.f;
-    }
-    BlockRegs<T, D> regs;
-    load_block<T, D>(regs, kbase, k0, u.L);
-    int buf = 0;
-    for (int kb = k0; kb < k1; kb += kBlock, buf ^= 1) {
-      store_block<T, D>(stage[buf], regs);
-      __syncthreads();   // block kb staged; every wave is done with the other buffer
-      if (kb + kBlock < k1) load_block<T, D>(regs, kbase, kb + kBlock, u.L);
-      if (kb + kBlock <= full_end)
-        stats_block<T, D, RTW, true>(p, u, rb, stage[buf], kb, col, grp, m, z);
-      else
-        stats_block<T, D, RTW, false>(p, u, rb, stage[buf], kb, col, grp, m, z);
-    }
-    __syncthreads();   // the stage is reused by the next row-tile group
-    // Merge the four lane groups that hold the same row, then store.
-#pragma unroll
-    for (int k = 0; k < RTW; ++k) {
-      const float M = group4_max(m[k]);
-      const float zz = (m[k] == -INFINITY) ? 0.f : z[k] * fast_exp2(m[k] - M);
-      const float Z = group4_sum(zz);
-      if (grp == 0 && tile0 + k < row_tiles) {
-        const int r = (tile0 + k) * 16 + col;
-        float *dst = p.row_part + ((u.ounit * p.chunks + chunk) * p.rows_pad + r) * 2;
-        dst[0] = M;
-        dst[1] = Z;
-      }
-    }
-  }
-}
-
-// Mass pass body for one 32-key block: S = Q.K^T, lane holds rows
-// (tile0 + k)*16 + 4*grp + i of key kb + kt*16 + col, so the lane sums its
-// rows in registers and only the four lane groups meet at the end.  Both
-// 16-key tiles are processed per row tile, so each row tile's normalisers are
-// read from LDS once per block; each key's sum still runs over the rows in
-// the same order.
-template <typename T, int D, int RTW, bool FULL>
-__device__ __forceinline__ void mass_block(const ScoreParams &p, const UnitInfo &u, const RowBlock<T, D, RTW> &rb,
-                                           const unsigned char *stage, int kb, int tile0, int col, int grp,
-                                           const float *smax, const float *sinv, float (&acc)[2]) {
-  using MF = Mfma<T>;
-  using Cfg = ScoreCfg<T, D>;
-  typename MF::frag kf[2][Cfg::steps];
-#pragma unroll
-  for (int kt = 0; kt < 2; ++kt) key_frags<T, D>(stage, kt, col, grp, kf[kt]);
-#pragma unroll
-  for (int k = 0; k < RTW; ++k) {
-    const float4 mx = *reinterpret_cast<const float4 *>(smax + k * 16 + 4 * grp);
-    const float4 iv = *reinterpret_cast<const float4 *>(sinv + k * 16 + 4 * grp);
-    const float rmax[4] = {mx.x, mx.y, mx.z, mx.w};
-    const float rinv[4] = {iv.x, iv.y, iv.z, iv.w};
-#pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-      const int key = kb + kt * 16 + col;
-      f32x4_t s = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int c = 0; c < Cfg::steps; ++c) s = MF::mma(rb.q[k][c], kf[kt][c], s);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float e = fast_exp2(fmaf(s[i], p.scale_log2, -rmax[i]));
-        if constexpr (FULL) {
-          acc[kt] = fmaf(e, rinv[i], acc[kt]);
-        } else {
-          const int r = (tile0 + k) * 16 + 4 * grp + i;
-          const int pos = u.L - p.w + r % p.w;
-          const bool vis = key < u.L && (!p.causal || key <= pos);
-          acc[kt] += vis ? e * rinv[i] : 0.f;
-        }
-      }
-    }
-  }
-}
-
-template <typename T, int D, int RTW>
-// Two workgroups per CU (two waves per SIMD): the window rows' normalisers sit
-// in LDS rather than registers, which (with a small spill) fits 256 registers
-// and measured faster than one wave per SIMD with everything in registers.
-__global__ __launch_bounds__(kThreads, 2) void score_mass_kernel(ScoreParams p) {
-  constexpr int n_waves = kWaves;
-  using Cfg = ScoreCfg<T, D>;
-  using RB = RowBlock<T, D, RTW>;
-  __shared__ __attribute__((aligned(16))) unsigned char stage[2][Cfg::stage_bytes];
-  __shared__ float part[kWaves][kScoreChunk];
-  __shared__ __attribute__((aligned(16))) float s_max[kWaves * RTW * 16];
-  __shared__ __attribute__((aligned(16))) float s_inv[kWaves * RTW * 16];
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
-  const int col = lane & 15, grp = lane >> 4;
-  int chunk, unit;
-  if (!xcd_chunk_unit(p, chunk, unit)) return;
-  const UnitInfo u = unit_info(p, unit);
-  const int k0 = chunk * kScoreChunk;
-  if (k0 >= u.L) return;
-  const int k1 = min(u.L, k0 + kScoreChunk);
-  const T *kbase = reinterpret_cast<const T *>(p.k) + u.cunit * p.cap * D;
-  const int row_tiles = p.rows_pad / 16;
-  const int full_end = p.causal ? min(u.L, u.L - p.w + 1) : u.L;
-
-  for (int tg = 0; tg < row_tiles; tg += n_waves * RTW) {
-    const int tile0 = tg + wave * RTW;
-    RB rb;
-    rb.load(p, u, tile0, col, grp);
-    // Normalisers of this group's rows, staged in LDS (absent rows: +inf, 0).
-    for (int i = threadIdx.x; i < kWaves * RTW * 16; i += kThreads) {
-      const int r = tg * 16 + i;
-      const bool in = r < p.rows_pad;
-      const float *st = p.row_stat + (u.ounit * p.rows_pad + (in ? r : 0)) * 2;
-      s_max[i] = in ? st[0] : INFINITY;
-      s_inv[i] = in ? st[1] : 0.f;
-    }
-    const float *smax = s_max + wave * RTW * 16;
-    const float *sinv = s_inv + wave * RTW * 16;
-    BlockRegs<T, D> regs;
-    load_block<T, D>(regs, kbase, k0, u.L);
-    int buf = 0;
-    for (int kb = k0; kb < k1; kb += kBlock, buf ^= 1) {
-      store_block<T, D>(stage[buf], regs);
-      __syncthreads();   // block kb staged; every wave is done with the other buffer
-      if (kb + kBlock < k1) load_block<T, D>(regs, kbase, kb + kBlock, u.L);
-      float acc[2] = {0.f, 0.f};
-      if (kb + kBlock <= full_end)
-        mass_block<T, D, RTW, true>(p, u, rb, stage[buf], kb, tile0, col, grp, smax, sinv, acc);
-      else
-        mass_block<T, D, RTW, false>(p, u, rb, stage[buf], kb, tile0, col, grp, smax, sinv, acc);
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-        const float tot = group4_sum_swap(acc[kt]);
-        if (grp == 0) {
-          // The first row group writes every column sum the final loop reads.
-          if (tg == 0) part[wave][kb - k0 + kt * 16 + col] = tot;
-          else part[wave][kb - k0 + kt * 16 + col] += tot;
-        }
-      }
-    }
-    __syncthreads();   // the stage is reused by the next row-tile group
-  }
-  __syncthreads();
-  float *out = p.scores + u.ounit * p.cap;
-  for (int j = threadIdx.x; j < k1 - k0; j += kThreads) {
-    float s = 0.f;
-#pragma unroll
-    for (int w = 0; w < n_waves; ++w) s += part[w][j];
-    out[k0 + j] = s;
-  }
-}
-
-// Row normalisers: (max, 1/sum) of every valid window row; absent rows get
-// (+inf, 0) so that the mass pass adds exactly zero for them.
-__global__ __launch_bounds__(kThreads) void score_rowmerge_kernel(ScoreParams p) {
-  const UnitInfo u = unit_info(p, blockIdx.y);
-  const int r = blockIdx.x * kThreads + threadIdx.x;
-  if (r >= p.rows_pad) return;
-  const int t = r % p.w;
-  const bool valid = r < p.rows && u.L - p.w + t >= 0;
-  const int active = (u.L + p.chunk_keys - 1) / p.chunk_keys;
-  float M = -INFINITY;
-  for (int c = 0; c < active; ++c) M = fmaxf(M, p.row_part[((u.ounit * p.chunks + c) * p.rows_pad + r) * 2]);
-  double Z = 0.0;
-  if (M != -INFINITY) {
-    for (int c = 0; c < active; ++c) {
-      const float *src = p.row_part + ((u.ounit * p.chunks + c) * p.rows_pad + r) * 2;
-      if (src[0] != -INFINITY) Z += static_cast<double>(src[1]) * static_cast<double>(fast_exp2(src[0] - M));
-    }
-  }
-  float *dst = p.row_stat + (u.ounit * p.rows_pad + r) * 2;
-  const bool ok = valid && M != -INFINITY && Z > 0.0;
-  dst[0] = ok ? M : INFINITY;
-  dst[1] = ok ? static_cast<float>(1.0 / Z) : 0.f;
-}
-
-// Row normalisers taken from the decode steps of the window tokens: the
-// (max, sum) pair decode wrote for query head g at position L - w + t is row
-// g * w + t's statistic; absent or empty rows get (+inf, 0) as above.
-__global__ __launch_bounds__(kThreads) void score_given_stats_kernel(ScoreParams p) {
-  const UnitInfo u = unit_info(p, blockIdx.y);
-  const int r = blockIdx.x * kThreads + threadIdx.x;
-  if (r >= p.rows_pad) return;
-  const int g = r / p.w;
-  const int t = r - g * p.w;
-  const bool valid = r < p.rows && u.L - p.w + t >= 0;
-  float M = INFINITY, Z = 0.f;
-  if (valid) {
-    const float *src =
-        p.given + ((((static_cast<size_t>(u.lc) * p.batch + u.b) * p.hq + u.h * p.group + g) * p.w) + t) * 2;
-    M = src[0];
-    Z = src[1];
-  }
-  const bool ok = valid && M != -INFINITY && M != INFINITY && Z > 0.f;
-  float *dst = p.row_stat + (u.ounit * p.rows_pad + r) * 2;
-  dst[0] = ok ? M : INFINITY;
-  dst[1] = ok ? 1.f / Z : 0.f;
-}
-
-
-// ---------------------------------------------------------------------------
-// Key-split kernels.  One workgroup of eight waves (two per SIMD) per CU,
-// resident for the whole call; the unit's window rows Q (and, for the mass
-// pass, each row's normaliser) are staged in LDS once per segment, and every
-// wave then walks its own groups of 64 keys: the group's K fragments are
-// loaded from global memory straight into registers in the MFMA operand
-// layout (the next group's while the current one is computed) and multiplied
-// against every row tile of Q read from LDS.  No barrier is needed inside the
-// key loop, and a wave covers all window rows of its keys, so each score is
-// summed in registers and written once.  Fragment element e of lane group grp
-// in step c is contraction index (4c + grp) * kpl + e, the same for Q and K,
-// so the four lane groups of a key read 4 * 16 consecutive bytes of its row
-// per load.
-// ---------------------------------------------------------------------------
-constexpr int kV2Waves = 8;
-constexpr int kV2Threads = kV2Waves * kWave;
-constexpr int kV2KT = 4;                  // 16-key tiles per wave group
-constexpr int kV2Group = kV2KT * 16;      // keys per wave group
-
-// The K fragments of one wave group and the Q fragments of one row tile.
-template <typename T, int D>
-struct V2Keys {
-  static constexpr int steps = D / (4 * Mfma<T>::kPerLane);
-  typename Mfma<T>::frag k[kV2KT][steps];
-};
-template <typename T, int D>
-struct V2Rows {
-  static constexpr int steps = D / (4 * Mfma<T>::kPerLane);
-  typename Mfma<T>::frag q[steps];
-};
-
-template <typename T, int D, int RTM>
-struct V2Cfg {
-  using MF = Mfma<T>;
-  using frag = typename MF::frag;
-  static constexpr int kpl = MF::kPerLane;
-  static constexpr int steps = D / (4 * kpl);           // MFMAs per 16x16 tile
-  static constexpr int row_bytes = D * (int)sizeof(T);
-  static constexpr int q_stride = row_bytes + 16;       // padded LDS pitch of a window row
-  static constexpr int max_rows = 16 * RTM;
+  static constexpr int pieces = row_bytes / 32;         // 16-byte pieces per lane of one row (two lanes share a row)
+  typedef uint4 frags[pieces];                          // a lane of one 32-row tile
+  static constexpr int KT = pieces <= 8 ? 2 : 1;        // 32-key tiles per wave group (64 K registers either way)
+  static constexpr int group = 32 * KT;                 // keys per wave group
+  static constexpr int q_stride = row_bytes + 16;       // LDS pitch of a window row: eight rows cover all banks
+  // Row tiles staged at once: the rows, the per-wave sums and the reference must fit the LDS of a CU.
+  static constexpr int max_tiles = row_bytes == 128 ? 28 : row_bytes == 256 ? 16 : 8;
+  static constexpr int max_rows = max_tiles * kTileRows;
   static constexpr int q_bytes = max_rows * q_stride;
-  static constexpr int merge_bytes = kV2Waves * max_rows * 2 * 4;   // per-wave row (reference, sum) of the statistics
-  static constexpr int const_bytes = max_rows * 2 * 4;             // row (max, 1/sum) of the mass pass
-  static constexpr int stage_bytes = q_bytes;
-  static constexpr int lds_bytes = q_bytes + (merge_bytes > const_bytes ? merge_bytes : const_bytes);
+  static constexpr int sum_bytes = kWaves * max_rows * 4;
+  static constexpr int stats_lds = q_bytes + sum_bytes + max_rows * 4;
+  static constexpr int mass_lds = q_bytes + max_rows * 8;
+  static constexpr int lost_keys = 4096;                // longest mass segment of a call with several row blocks
+  static_assert(stats_lds <= 160 * 1024 && mass_lds + lost_keys * 4 + kWaves * kWave * 4 + 16 <= 160 * 1024, "window rows and statistics fit one CU's LDS");
 };
 
-// Window rows of the unit into LDS (rows that do not exist are zero).  A
-// thread's loads go out in two batches, each issued before its stores, so
-// the staging costs two memory round trips and few registers; absent rows
-// load the unit's first window row (always a valid address) and store zero.
-template <typename T, int D, int RTM>
-__device__ __forceinline__ void v2_stage_window(const ScoreParams &p, const UnitInfo &u, unsigned char *qs) {
-  using C = V2Cfg<T, D, RTM>;
-  constexpr int pieces = C::row_bytes / 16;
-  constexpr int per_thread = (C::max_rows * pieces + kV2Threads - 1) / kV2Threads;
-  constexpr int half = (per_thread + 1) / 2;
-  const unsigned char *base = reinterpret_cast<const unsigned char *>(p.q_win) +
-      (((size_t)u.lc * p.batch + u.b) * p.hq + (size_t)u.h * p.group) * p.w * (size_t)C::row_bytes;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    uint4 v[half];
-    bool ok[half];
-#pragma unroll
-    for (int j = 0; j < half; ++j) {
-      const int i = (h * half + j) * kV2Threads + static_cast<int>(threadIdx.x);
-      const int r = i / pieces;
-      const int pc = i - r * pieces;
-      const int g = r / p.w;
-      const int t = r - g * p.w;
-      ok[j] = (h * half + j < per_thread) && r < p.rows && u.L - p.w + t >= 0;
-      // row g * w + t of the unit's group is window row t of query head h * G + g
-      const size_t off = ok[j] ? (static_cast<size_t>(r) * C::row_bytes + pc * 16) : 0;
-      v[j] = *reinterpret_cast<const uint4 *>(base + off);
-    }
-#pragma unroll
-    for (int j = 0; j < half; ++j) {
-      const int i = (h * half + j) * kV2Threads + static_cast<int>(threadIdx.x);
-      const int r = i / pieces;
-      if (h * half + j < per_thread)
-        *reinterpret_cast<uint4 *>(qs + r * C::q_stride + (i - r * pieces) * 16) = ok[j] ? v[j] : make_uint4(0, 0, 0, 0);
-    }
-  }
-}
-
-// K fragments of the wave group at g0 (keys at or past L read row 0 of the
-// unit and are masked by the caller).
-template <typename T, int D>
-__device__ __forceinline__ void v2_load_keys(V2Keys<T, D> &kf, const T *kbase, int g0, int L, int col, int grp) {
-  constexpr int kpl = Mfma<T>::kPerLane;
-#pragma unroll
-  for (int kt = 0; kt < kV2KT; ++kt) {
-    const int key = g0 + kt * 16 + col;
-    const T *src = kbase + static_cast<size_t>(key < L ? key : 0) * D + grp * kpl;
-#pragma unroll
-    for (int c = 0; c < V2Keys<T, D>::steps; ++c) kf.k[kt][c] = load_frag(src + c * 4 * kpl);
-  }
-}
-
-template <typename T, int D>
-__device__ __forceinline__ void v2_load_q(V2Rows<T, D> &qf, const unsigned char *qs, int rt, int col, int grp) {
-  constexpr int kpl = Mfma<T>::kPerLane;
-  constexpr int q_stride = D * (int)sizeof(T) + 16;
-  const T *row = reinterpret_cast<const T *>(qs + (rt * 16 + col) * q_stride) + grp * kpl;
-#pragma unroll
-  for (int c = 0; c < V2Rows<T, D>::steps; ++c) qf.q[c] = load_frag(row + c * 4 * kpl);
-}
-
-// Mass of one row tile for one wave group: S = Q.K^T, lane (col, grp) holds
-// rows 16 rt + 4 grp + i of key g0 + 16 kt + col and adds exp2(x - max) / sum
-// of those rows into acc[kt].
-template <typename T, int D, bool FULL>
-__device__ __forceinline__ void v2_mass_tile(const ScoreParams &p, const UnitInfo &u, const V2Rows<T, D> &qf,
-                                             const float4 mx, const float4 iv, const V2Keys<T, D> &kf, int g0,
-                                             int rt, int col, int grp, float (&acc)[kV2KT]) {
-  using MF = Mfma<T>;
-  const float rmax[4] = {mx.x, mx.y, mx.z, mx.w};
-  const float rinv[4] = {iv.x, iv.y, iv.z, iv.w};
-#pragma unroll
-  for (int kt = 0; kt < kV2KT; ++kt) {
-    f32x4_t s = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int c = 0; c < V2Keys<T, D>::steps; ++c) s = MF::mma(qf.q[c], kf.k[kt][c], s);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float e = fast_exp2(fmaf(s[i], p.scale_log2, -rmax[i]));
-      if constexpr (FULL) {
-        acc[kt] = fmaf(e, rinv[i], acc[kt]);
-      } else {
-        const int r = rt * 16 + 4 * grp + i;
-        const int pos = u.L - p.w + r % p.w;
-        const int key = g0 + kt * 16 + col;
-        const bool vis = key < u.L && (!p.causal || key <= pos);
-        acc[kt] += vis ? e * rinv[i] : 0.f;
-      }
-    }
-  }
-}
-
-template <typename T, int D, bool FULL>
-__device__ __forceinline__ void v2_mass_group(const ScoreParams &p, const UnitInfo &u, const unsigned char *qs,
-                                              const float *cmx, const float *cin, const V2Keys<T, D> &kf, int g0,
-                                              int row_tiles, int col, int grp, float (&acc)[kV2KT]) {
-  for (int rt = 0; rt < row_tiles; rt += 2) {
-    V2Rows<T, D> qa, qb;
-    v2_load_q<T, D>(qa, qs, rt, col, grp);
-    v2_load_q<T, D>(qb, qs, rt + 1, col, grp);
-    const float4 ma = *reinterpret_cast<const float4 *>(cmx + rt * 16 + 4 * grp);
-    const float4 ia = *reinterpret_cast<const float4 *>(cin + rt * 16 + 4 * grp);
-    const float4 mb = *reinterpret_cast<const float4 *>(cmx + rt * 16 + 16 + 4 * grp);
-    const float4 ib = *reinterpret_cast<const float4 *>(cin + rt * 16 + 16 + 4 * grp);
-    v2_mass_tile<T, D, FULL>(p, u, qa, ma, ia, kf, g0, rt, col, grp, acc);
-    v2_mass_tile<T, D, FULL>(p, u, qb, mb, ib, kf, g0, rt + 1, col, grp, acc);
-  }
-}
-
-// Work of the key-split kernels: the non-empty chunks of chunk_keys keys of
-// every unit (a unit of length L has ceil(L / chunk_keys) of them), taken
-// unit-major.  The grid is persistent (one workgroup per CU, all resident for
-// the whole call) and workgroup b takes an equal share of those chunks, a
-// contiguous run [c_begin, c_end) of the global order; it walks the run as
-// segments, the maximal pieces inside one unit, so the window rows are
-// staged once per segment and a segment's key loop needs no barrier.
-struct V2Run {
-  int unit;       // unit of the run's first chunk
-  int chunk;      // that chunk's index within its unit
-  long long n;    // chunks in the run
+// ---------------------------------------------------------------------------
+// Shares of the persistent grid.  The work is the non-empty chunks of
+// chunk_keys keys of every unit (ceil(L / chunk_keys) of them), unit-major.
+// Workgroup b takes chunks [total * b / grid, total * (b + 1) / grid) of that
+// order and walks them as segments, the pieces inside one unit.
+// ---------------------------------------------------------------------------
+struct Share {
+  int b;             // rank of the workgroup in the chunk order
+  int unit;          // unit of the next chunk
+  int chunk;         // that chunk's index within its unit
+  long long n;       // chunks left
+  long long before;  // chunks of all units before `unit`
+  long long total;   // chunks of all units
 };
 
-// Every workgroup scans the units' lengths (a block-wide prefix sum of the
-// chunk counts) to find where its share starts.  `scan` is LDS scratch of
-// kV2Threads + 2 entries.
-__device__ V2Run v2_run(const ScoreParams &p, long long *scan) {
+// A value that is the same in every lane, kept in a scalar register.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ long long uniform(long long v) {
+  const unsigned lo = uniform(static_cast<int>(v)), hi = uniform(static_cast<int>(v >> 32));
+  return static_cast<long long>(static_cast<unsigned long long>(hi) << 32 | lo);
+}
+
+__device__ __forceinline__ int unit_len(const ScoreParams &p, int unit) {
+  const int L = p.len[static_cast<size_t>(p.layer0) * p.batch * p.hkv + unit];
+  return L < 0 ? 0 : (L > p.cap ? p.cap : L);
+}
+
+__device__ __forceinline__ int unit_chunks(const ScoreParams &p, int unit) {
+  return (unit_len(p, unit) + p.chunk_keys - 1) / p.chunk_keys;
+}
+
+__device__ __forceinline__ long long share_begin(long long total, int b) {
+  return total * b / static_cast<int>(gridDim.x);
+}
+
+// Every workgroup scans the units' chunk counts to find where its share
+// starts.  `lds`: kWaves + 3 entries of scratch.
+__device__ Share find_share(const ScoreParams &p, long long *lds) {
   const int units = p.n_layers * p.batch * p.hkv;
-  const int per_t = (units + kV2Threads - 1) / kV2Threads;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int per_t = (units + kThreads - 1) / kThreads;
   const int u0 = min(units, static_cast<int>(threadIdx.x) * per_t);
   const int u1 = min(units, u0 + per_t);
   long long mine = 0;
-  for (int u = u0; u < u1; ++u) mine += (unit_info(p, u).L + p.chunk_keys - 1) / p.chunk_keys;
-  scan[threadIdx.x] = mine;
-  __syncthreads();
-  // Inclusive scan (Hillis-Steele) over the thread totals.
-  for (int off = 1; off < kV2Threads; off <<= 1) {
-    const long long v = static_cast<int>(threadIdx.x) >= off ? scan[threadIdx.x - off] : 0;
-    __syncthreads();
-    scan[threadIdx.x] += v;
-    __syncthreads();
+  for (int u = u0; u < u1; ++u) mine += unit_chunks(p, u);
+  long long incl = mine;
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    const long long o = __shfl_up(incl, d, kWave);
+    if (lane >= d) incl += o;
   }
-  const long long total = scan[kV2Threads - 1];
-  const long long b0 = total * blockIdx.x / gridDim.x;
-  const long long b1 = total * (blockIdx.x + 1) / gridDim.x;
-  const long long before = threadIdx.x ? scan[threadIdx.x - 1] : 0;
+  if (lane == kWave - 1) lds[wave] = incl;
+  if (threadIdx.x == 0) lds[kWaves] = units;       // an empty share starts past the last unit
   __syncthreads();
-  if (threadIdx.x == 0) {
-    scan[kV2Threads] = units;            // no chunk of this run: past the last unit
-    scan[kV2Threads + 1] = 0;
+  long long total = 0, excl = incl - mine;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    if (w < wave) excl += lds[w];
+    total += lds[w];
   }
-  __syncthreads();
-  if (b0 < b1 && before <= b0 && b0 < before + mine) {
-    long long c = before;
+  // Consecutive workgroup ids go to the eight XCDs in turn; neighbouring
+  // shares (which stage the same units' window rows) are kept on one XCD's L2.
+  const int g = static_cast<int>(gridDim.x);
+  Share s;
+  s.b = g % 8 == 0 ? static_cast<int>(blockIdx.x % 8) * (g / 8) + static_cast<int>(blockIdx.x / 8)
+                   : static_cast<int>(blockIdx.x);
+  total = uniform(total);
+  const long long b0 = share_begin(total, s.b), b1 = share_begin(total, s.b + 1);
+  if (b0 < b1 && excl <= b0 && b0 < excl + mine) {
+    long long c = excl;
     for (int u = u0; u < u1; ++u) {
-      const int nc = (unit_info(p, u).L + p.chunk_keys - 1) / p.chunk_keys;
+      const int nc = unit_chunks(p, u);
       if (b0 < c + nc) {
-        scan[kV2Threads] = u;
-        scan[kV2Threads + 1] = static_cast<int>(b0 - c);
+        lds[kWaves] = u;
+        lds[kWaves + 1] = b0 - c;
+        lds[kWaves + 2] = c;
         break;
       }
       c += nc;
     }
   }
   __syncthreads();
-  V2Run r;
-  r.unit = static_cast<int>(scan[kV2Threads]);
-  r.chunk = static_cast<int>(scan[kV2Threads + 1]);
-  r.n = b1 - b0;
-  __syncthreads();                       // the scratch is reused by the caller
-  return r;
+  s.unit = uniform(static_cast<int>(lds[kWaves]));
+  s.chunk = uniform(static_cast<int>(lds[kWaves + 1]));
+  s.before = uniform(lds[kWaves + 2]);
+  s.n = b1 - b0;
+  s.total = total;
+  __syncthreads();                                 // the scratch is reused by the caller
+  return s;
 }
 
-// Next segment of a run: chunks [c0, c1) of `unit`, consuming them from the
-// run.  Returns false when the run is exhausted.
-__device__ __forceinline__ bool v2_next_segment(const ScoreParams &p, V2Run &r, int &unit, int &c0, int &c1) {
+struct Segment {
+  int unit, L;
+  int k0, k1;              // its keys
+  long long before;        // chunks of all units before its unit
+};
+
+// Next segment of the share, of at most max_keys keys; false when the share is
+// exhausted.
+__device__ __forceinline__ bool next_segment(const ScoreParams &p, Share &s, Segment &seg, int max_keys = 1 << 30) {
   const int units = p.n_layers * p.batch * p.hkv;
-  while (r.n > 0 && r.unit < units) {
-    const int nc = (unit_info(p, r.unit).L + p.chunk_keys - 1) / p.chunk_keys;
-    if (r.chunk < nc) {
-      const long long take = min(static_cast<long long>(nc - r.chunk), r.n);
-      unit = r.unit;
-      c0 = r.chunk;
-      c1 = r.chunk + static_cast<int>(take);
-      r.n -= take;
-      r.chunk = 0;
-      ++r.unit;
+  while (s.n > 0 && s.unit < units) {
+    const int L = unit_len(p, s.unit);
+    const int nc = (L + p.chunk_keys - 1) / p.chunk_keys;
+    seg.unit = s.unit;
+    seg.L = L;
+    seg.before = s.before;
+    const int c0 = s.chunk;
+    if (c0 < nc) {
+      const int take =
+          min(static_cast<int>(min(static_cast<long long>(nc - c0), s.n)), max_keys / p.chunk_keys);
+      seg.k0 = c0 * p.chunk_keys;
+      seg.k1 = min(L, (c0 + take) * p.chunk_keys);
+      s.n -= take;
+      s.chunk += take;
       return true;
     }
-    r.chunk = 0;
-    ++r.unit;
+    s.chunk = 0;
+    s.before += nc;
+    ++s.unit;
   }
   return false;
 }
 
-template <typename T, int D, int RTM>
-__global__ __launch_bounds__(kV2Threads, 1) void score_mass_v2_kernel(ScoreParams p) {
-  using C = V2Cfg<T, D, RTM>;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[C::lds_bytes];
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
-  const int col = lane & 15, grp = lane >> 4;
-  unsigned char *qs = smem;
-  V2Run run = v2_run(p, reinterpret_cast<long long *>(smem));
-  float *cmx = reinterpret_cast<float *>(smem + C::stage_bytes);
-  float *cin = cmx + C::max_rows;
-  const int row_tiles = (p.rows_pad / 16 + 1) & ~1;
-  constexpr int stride = kV2Waves * kV2Group;
-  int sunit, sc0, sc1;
-  while (v2_next_segment(p, run, sunit, sc0, sc1)) {
-    const UnitInfo u = unit_info(p, sunit);
-    const int k0 = sc0 * p.chunk_keys;
-    const int k1 = min(u.L, sc1 * p.chunk_keys);
-    const T *kbase = reinterpret_cast<const T *>(p.k) + u.cunit * p.cap * D;
-    __syncthreads();                        // every wave is done with the previous segment's rows
-    v2_stage_window<T, D, RTM>(p, u, qs);
-    for (int r = threadIdx.x; r < row_tiles * 16; r += kV2Threads) {
-      const bool in = r < p.rows_pad;
-      const float *st = p.row_stat + (u.ounit * p.rows_pad + (in ? r : 0)) * 2;
-      cmx[r] = in ? st[0] : INFINITY;
-      cin[r] = in ? st[1] : 0.f;
-    }
-    int g0 = k0 + wave * kV2Group;
-    V2Keys<T, D> kf;
-    v2_load_keys<T, D>(kf, kbase, g0 < k1 ? g0 : k0, u.L, col, grp);
-    __syncthreads();
-    const int full_end = p.causal ? min(u.L, u.L - p.w + 1) : u.L;
-    float *out = p.scores + u.ounit * p.cap;
-    for (; g0 < k1; g0 += stride) {
-      V2Keys<T, D> kn;
-      const int gn = g0 + stride;
-      v2_load_keys<T, D>(kn, kbase, gn < k1 ? gn : g0, u.L, col, grp);
-      float acc[kV2KT] = {0.f, 0.f, 0.f, 0.f};
-      if (g0 + kV2Group <= full_end)
-        v2_mass_group<T, D, true>(p, u, qs, cmx, cin, kf, g0, row_tiles, col, grp, acc);
-      else
-        v2_mass_group<T, D, false>(p, u, qs, cmx, cin, kf, g0, row_tiles, col, grp, acc);
+// The statistics of workgroup b's segment of a unit go to partial slot b +
+// unit: along the chunk order every new segment raises b, the unit or both,
+// so the slots of all segments differ, and grid + units - 1 slots hold them.
+
+// ---------------------------------------------------------------------------
+// Tiles.  Piece c of lane (l32, half) is the 16 bytes at 32 c + 16 half of its
+// row: the contraction order is the same permutation for K and Q.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ f32x16_t mma_piece(bf16_t, uint4 k, uint4 q, f32x16_t c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, k), __builtin_bit_cast(bf16x8_t, q), c,
+                                                 0, 0, 0);
+}
+__device__ __forceinline__ f32x16_t mma_piece(float, uint4 k, uint4 q, f32x16_t c) {
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(k.x), __uint_as_float(q.x), c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(k.y), __uint_as_float(q.y), c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(k.z), __uint_as_float(q.z), c, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(k.w), __uint_as_float(q.w), c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x16_t zero16() {
+  f32x16_t z;
 #pragma unroll
-      for (int kt = 0; kt < kV2KT; ++kt) {
-        const float tot = group4_sum_swap(acc[kt]);
-        const int key = g0 + kt * 16 + col;
-        if (grp == 0 && key < k1) out[key] = tot;
-      }
-      kf = kn;
+  for (int i = 0; i < 16; ++i) z[i] = 0.f;
+  return z;
+}
+
+// Key of accumulator register i of a tile at key kb.
+__device__ __forceinline__ int tile_key(int kb, int i, int half) { return kb + 8 * (i >> 2) + 4 * half + (i & 3); }
+
+template <typename T, int D>
+struct Keys {
+  typename ScoreCfg<T, D>::frags k[ScoreCfg<T, D>::KT];
+};
+template <typename T, int D>
+struct Rows {
+  typename ScoreCfg<T, D>::frags q;
+};
+
+// Where a wave's K fragments come from: the unit's rows and its length (keys
+// at or past it read row 0 and are masked by the caller).
+struct KeySource {
+  const unsigned char *base;
+  int L, l32, half;
+};
+
+template <typename T, int D>
+__device__ __forceinline__ void load_key_tile(typename ScoreCfg<T, D>::frags &k, const KeySource &src, int kb) {
+  const int key = kb + src.l32;
+  const unsigned char *row =
+      src.base + static_cast<size_t>(key < src.L ? key : 0) * ScoreCfg<T, D>::row_bytes + src.half * 16;
+#pragma unroll
+  for (int c = 0; c < ScoreCfg<T, D>::pieces; ++c) k[c] = *reinterpret_cast<const uint4 *>(row + c * 32);
+}
+template <typename T, int D>
+__device__ __forceinline__ void load_keys(Keys<T, D> &kf, const KeySource &src, int g0) {
+#pragma unroll
+  for (int kt = 0; kt < ScoreCfg<T, D>::KT; ++kt) load_key_tile<T, D>(kf.k[kt], src, g0 + kt * 32);
+}
+
+// `qrow`: the lane's row of row tile 0 (plus 16 bytes for the upper half).
+template <typename T, int D>
+__device__ __forceinline__ uint4 q_piece(const unsigned char *qrow, int rt, int c) {
+  return *reinterpret_cast<const uint4 *>(qrow + rt * kTileRows * ScoreCfg<T, D>::q_stride + c * 32);
+}
+template <typename T, int D>
+__device__ __forceinline__ void load_rows(Rows<T, D> &r, const unsigned char *qrow, int rt) {
+#pragma unroll
+  for (int c = 0; c < ScoreCfg<T, D>::pieces; ++c) r.q[c] = q_piece<T, D>(qrow, rt, c);
+}
+
+template <typename T, int D>
+__device__ __forceinline__ f32x16_t tile_products(const typename ScoreCfg<T, D>::frags &k, const Rows<T, D> &r) {
+  f32x16_t s = zero16();
+#pragma unroll
+  for (int c = 0; c < ScoreCfg<T, D>::pieces; ++c) s = mma_piece(T{}, k[c], r.q[c], s);
+  return s;
+}
+
+// One pipeline phase: the products of one tile into `s`, and between them the
+// work on the previous tile's 16 registers: arg(x), exp2, add(i, e), each step
+// one slot after the one before so that no instruction waits for its operand.
+// RELOAD replaces each Q fragment by the one of row tile `next` after its last
+// use.
+template <typename T, int D, bool RELOAD, typename Arg, typename Add>
+__device__ __forceinline__ void phase(f32x16_t &s, const typename ScoreCfg<T, D>::frags &k, Rows<T, D> &r,
+                                      const unsigned char *qrow, int next, const f32x16_t &prev, Arg arg, Add add) {
+  constexpr int P = ScoreCfg<T, D>::pieces;
+  constexpr int per = 16 / P;
+  float t[16];
+  s = zero16();
+#pragma unroll
+  for (int c = 0; c < P; ++c) {
+    s = mma_piece(T{}, k[c], r.q[c], s);
+    if constexpr (RELOAD) r.q[c] = q_piece<T, D>(qrow, next, c);
+#pragma unroll
+    for (int e = 0; e < per; ++e) {
+      if (c >= 2) add((c - 2) * per + e, t[(c - 2) * per + e]);
+      if (c >= 1) t[(c - 1) * per + e] = fast_exp2(t[(c - 1) * per + e]);
+      t[c * per + e] = arg(prev[c * per + e]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int e = 0; e < per; ++e) {
+    add((P - 2) * per + e, t[(P - 2) * per + e]);
+    t[(P - 1) * per + e] = fast_exp2(t[(P - 1) * per + e]);
+  }
+#pragma unroll
+  for (int e = 0; e < per; ++e) add((P - 1) * per + e, t[(P - 1) * per + e]);
+}
+
+// A wave's row tiles rt0, rt0 + step, ... < tiles (at least one) of one group,
+// pipelined: begin(rt) before the tile's first use, arg and add(kt, i, e) as in
+// phase for register i of key tile kt, end(rt) after its last.  Each K
+// fragment is replaced by the one of the group at `next` (none if negative)
+// after its last use, so that these loads run under the last tile's
+// exponentials and the other wave's work.
+template <typename T, int D, typename Begin, typename Arg, typename Add, typename End>
+__device__ __forceinline__ void walk_rows(Keys<T, D> &kf, const KeySource &src, int next, const unsigned char *qrow,
+                                          int rt0, int step, int tiles, Begin begin, Arg arg, Add add, End end) {
+  constexpr int KT = ScoreCfg<T, D>::KT;
+  Rows<T, D> r;
+  load_rows<T, D>(r, qrow, rt0);
+  const auto add0 = [&](int i, float e) { add(0, i, e); };
+  const auto add1 = [&](int i, float e) { add(1, i, e); };
+  f32x16_t s0, s1;
+  s0 = tile_products<T, D>(kf.k[0], r);
+  int rt = rt0;
+  if constexpr (KT == 2) {
+    for (; rt + step < tiles; rt += step) {
+      begin(rt);
+      phase<T, D, true>(s1, kf.k[1], r, qrow, rt + step, s0, arg, add0);
+      phase<T, D, false>(s0, kf.k[0], r, qrow, 0, s1, arg, add1);
+      end(rt);
+    }
+    if (next >= 0) load_key_tile<T, D>(kf.k[0], src, next);
+    begin(rt);
+    phase<T, D, false>(s1, kf.k[1], r, qrow, 0, s0, arg, add0);
+    if (next >= 0) load_key_tile<T, D>(kf.k[1], src, next + 32);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) add1(i, fast_exp2(arg(s1[i])));
+    end(rt);
+  } else {
+    if (rt0 + step < tiles) load_rows<T, D>(r, qrow, rt0 + step);
+    for (; rt + step < tiles; rt += step) {
+      begin(rt);
+      phase<T, D, true>(s1, kf.k[0], r, qrow, min(rt + 2 * step, tiles - 1), s0, arg, add0);
+      end(rt);
+      s0 = s1;
+    }
+    if (next >= 0) load_key_tile<T, D>(kf.k[0], src, next);
+    begin(rt);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) add0(i, fast_exp2(arg(s0[i])));
+    end(rt);
+  }
+}
+
+// How the waves of a workgroup split a segment: row_waves waves share a group's
+// row tiles (1 when the segment has a group for every wave; more in small
+// calls, whose segments have fewer), the other factor takes different groups.
+template <typename T, int D>
+__device__ __forceinline__ int row_waves(const Segment &seg, int tiles) {
+  const int groups = (seg.k1 - seg.k0 + ScoreCfg<T, D>::group - 1) / ScoreCfg<T, D>::group;
+  int rw = 1;
+  while (2 * rw * groups <= kWaves && 2 * rw <= tiles) rw *= 2;
+  return rw;
+}
+
+// threadIdx.x, hidden from the optimiser: addresses derived from it are
+// computed where they are used instead of being kept in registers (and
+// spilled) across the key loop.
+__device__ __forceinline__ int thread_id() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+// Row block [r0, r0 + 32 * tiles) of the unit's window rows into LDS (rows
+// that do not exist are zero).  Loads go out in batches ahead of their stores.
+template <typename T, int D>
+__device__ __forceinline__ void stage_rows(const ScoreParams &p, const Segment &seg, unsigned char *qs, int r0,
+                                           int tiles) {
+  using C = ScoreCfg<T, D>;
+  constexpr int pieces = C::row_bytes / 16;
+  constexpr int kBatch = 7;
+  const unsigned char *base = reinterpret_cast<const unsigned char *>(p.q_win) +
+                              static_cast<size_t>(seg.unit) * p.rows * C::row_bytes;
+  const int n = tiles * kTileRows * pieces;
+  const int tid = thread_id();
+  for (int i0 = 0; i0 < n; i0 += kBatch * kThreads) {
+    uint4 v[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int i = i0 + j * kThreads + tid;
+      const int r = r0 + i / pieces;
+      const bool ok = i < n && r < p.rows && (seg.L >= p.w || seg.L - p.w + r % p.w >= 0);
+      v[j] = ok ? *reinterpret_cast<const uint4 *>(base + static_cast<size_t>(r) * C::row_bytes + (i % pieces) * 16)
+                : make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int i = i0 + j * kThreads + tid;
+      if (i < n) *reinterpret_cast<uint4 *>(qs + (i / pieces) * C::q_stride + (i % pieces) * 16) = v[j];
     }
   }
 }
 
-// Statistics of one row tile for one wave group: S^T = K.Q^T, lane (col,
-// grp) holds keys g0 + 16 kt + 4 grp + i of row 16 rt + col.  Each wave keeps,
-// per window row, a reference m and the sum z of 2^(x - m) over its keys in
-// LDS (mrow, zrow).  On the wave's first group (MODE 0) m is the row's
-// largest logit among the group's first 16 keys, so the largest term of
-// every sum is at least 1, and later groups (MODE 1) only add terms, with no
-// running maximum.  A logit more than about 120 above m overflows a sum;
-// the caller then redoes the wave's keys with a running maximum (MODE 2).
-template <typename T, int D, bool FULL, int MODE>
-__device__ __forceinline__ void v2_stats_tile(const ScoreParams &p, const UnitInfo &u, const V2Rows<T, D> &qf,
-                                              const V2Keys<T, D> &kf, int g0, int rt, int col, int grp, float m_in,
-                                              float z_in, float *mrow, float *zrow) {
-  using MF = Mfma<T>;
+template <typename T, int D>
+__device__ __forceinline__ KeySource key_source(const ScoreParams &p, const Segment &seg, int l32, int half) {
+  const size_t cunit = static_cast<size_t>(p.layer0) * p.batch * p.hkv + seg.unit;
+  return KeySource{reinterpret_cast<const unsigned char *>(p.k) + cunit * p.cap * ScoreCfg<T, D>::row_bytes, seg.L,
+                   l32, half};
+}
+
+// Row blocks of a unit: the fewest that fit the LDS stage, of equal size.
+template <typename T, int D>
+__device__ __forceinline__ int block_tiles(const ScoreParams &p) {
+  const int tiles = (p.rows + kTileRows - 1) / kTileRows;
+  const int blocks = (tiles + ScoreCfg<T, D>::max_tiles - 1) / ScoreCfg<T, D>::max_tiles;
+  return (tiles + blocks - 1) / blocks;
+}
+
+// Last key that window row r sees (-1 or less: none).
+__device__ __forceinline__ int last_visible(const ScoreParams &p, int L, int r) {
+  return p.causal ? L - p.w + r % p.w : L - 1;
+}
+
+// Keys every valid window row sees: below L, and (causal) up to L - w.
+__device__ __forceinline__ int full_end(const ScoreParams &p, int L) { return p.causal ? min(L, L - p.w + 1) : L; }
+
+// ---------------------------------------------------------------------------
+// Statistics pass.  Every row keeps a reference m, the largest logit among the
+// segment's first 32 keys (finite unless the row sees no key of the segment),
+// and sums 2^(x - m) over the segment's keys: no running maximum per key, and
+// the largest term is at least 1.  A logit more than about 120 above m
+// overflows a sum; the segment is then done again with its exact maxima.
+// ---------------------------------------------------------------------------
+
+// Largest visible logit of the lane's row in one tile at key kb (lim: the last
+// key the row sees).
+__device__ __forceinline__ float tile_max(const ScoreParams &p, const f32x16_t &s, int kb, int lim, int half) {
+  float m = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) m = fmaxf(m, tile_key(kb, i, half) <= lim ? s[i] * p.scale_log2 : -INFINITY);
+  return m;
+}
+
+// max over the two lane halves (lanes l and l ^ 32 hold the same row).
+__device__ __forceinline__ float half_max(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+__device__ __forceinline__ float half_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Sums (or, with MAX, maxima) of a wave's groups, per row in `acc`.
+template <typename T, int D, bool MAX>
+__device__ __forceinline__ void stats_groups(const ScoreParams &p, const Segment &seg, const KeySource &src,
+                                             const unsigned char *qrow, const float *mref, float *acc, int r0,
+                                             int tiles, int wave, int rw) {
+  using C = ScoreCfg<T, D>;
+  const int stride = kWaves / rw * C::group;
+  const int rt0 = wave % rw;
+  const int l32 = src.l32, half = src.half;
   const float c = p.scale_log2;
-  const int r = rt * 16 + col;
-  f32x4_t s[kV2KT];
+  const int end = full_end(p, seg.L);
+  int g0 = seg.k0 + wave / rw * C::group;
+  if (g0 >= seg.k1) return;
+  Keys<T, D> kf;
+  load_keys<T, D>(kf, src, g0);
+  for (; g0 < seg.k1; g0 += stride) {
+    const int next = g0 + stride < seg.k1 ? g0 + stride : -1;
+    if constexpr (MAX) {
+      for (int rt = rt0; rt < tiles; rt += rw) {
+        Rows<T, D> r;
+        load_rows<T, D>(r, qrow, rt);
+        const int lim = last_visible(p, seg.L, r0 + rt * kTileRows + l32);
+        float a = acc[rt * kTileRows];
 #pragma unroll
-  for (int kt = 0; kt < kV2KT; ++kt) {
-    s[kt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int cc = 0; cc < V2Keys<T, D>::steps; ++cc) s[kt] = MF::mma(kf.k[kt][cc], qf.q[cc], s[kt]);
-  }
-  bool vis[kV2KT][4];
-  const int pos = u.L - p.w + r % p.w;
-#pragma unroll
-  for (int kt = 0; kt < kV2KT; ++kt)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if constexpr (FULL) {
-        vis[kt][i] = true;
-      } else {
-        const int key = g0 + kt * 16 + 4 * grp + i;
-        vis[kt][i] = key < u.L && (!p.causal || key <= pos);
+        for (int kt = 0; kt < C::KT; ++kt)
+          a = fmaxf(a, tile_max(p, tile_products<T, D>(kf.k[kt], r), g0 + kt * 32, lim, half));
+        acc[rt * kTileRows] = half_max(a);
       }
-    }
-  float m = m_in, zold = z_in;
-  if constexpr (MODE == 0) {
-    float lm = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) lm = fmaxf(lm, vis[0][i] ? s[0][i] * c : -INFINITY);
-    m = group4_max(lm);
-    zold = 0.f;
-  } else if constexpr (MODE == 2) {
-    float lm = -INFINITY;
-#pragma unroll
-    for (int kt = 0; kt < kV2KT; ++kt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) lm = fmaxf(lm, vis[kt][i] ? s[kt][i] * c : -INFINITY);
-    const float mn = fmaxf(m_in, group4_max(lm));
-    zold = (m_in == -INFINITY || mn == -INFINITY) ? 0.f : z_in * fast_exp2(m_in - mn);
-    m = mn;
-  }
-  float zz = 0.f;
-  if (MODE != 2 || m != -INFINITY) {
-#pragma unroll
-    for (int kt = 0; kt < kV2KT; ++kt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float e = fast_exp2(fmaf(s[kt][i], c, -m));
-        if constexpr (FULL) zz += e;
-        else zz += vis[kt][i] ? e : 0.f;
-      }
-  }
-  const float zsum = group4_sum_swap(zz);
-  if (grp == 0) {
-    mrow[r] = m;
-    zrow[r] = zold + zsum;
-  }
-}
-
-template <typename T, int D, bool FULL, int MODE>
-__device__ __forceinline__ void v2_stats_group(const ScoreParams &p, const UnitInfo &u, const unsigned char *qs,
-                                               const V2Keys<T, D> &kf, int g0, int row_tiles, int col, int grp,
-                                               float *mrow, float *zrow) {
-  for (int rt = 0; rt < row_tiles; rt += 2) {
-    V2Rows<T, D> qa, qb;
-    v2_load_q<T, D>(qa, qs, rt, col, grp);
-    v2_load_q<T, D>(qb, qs, rt + 1, col, grp);
-    float ma = 0.f, za = 0.f, mb = 0.f, zb = 0.f;
-    if constexpr (MODE != 0) {
-      ma = mrow[rt * 16 + col];
-      za = zrow[rt * 16 + col];
-      mb = mrow[rt * 16 + 16 + col];
-      zb = zrow[rt * 16 + 16 + col];
-    }
-    v2_stats_tile<T, D, FULL, MODE>(p, u, qa, kf, g0, rt, col, grp, ma, za, mrow, zrow);
-    v2_stats_tile<T, D, FULL, MODE>(p, u, qb, kf, g0, rt + 1, col, grp, mb, zb, mrow, zrow);
-  }
-}
-
-// All groups of a wave's keys; ONLINE selects the running-maximum form.
-template <typename T, int D, bool ONLINE>
-__device__ __forceinline__ void v2_stats_keys(const ScoreParams &p, const UnitInfo &u, const unsigned char *qs,
-                                              const T *kbase, int gstart, int k1, int full_end, int row_tiles,
-                                              int col, int grp, float *mrow, float *zrow) {
-  constexpr int stride = kV2Waves * kV2Group;
-  V2Keys<T, D> kf;
-  v2_load_keys<T, D>(kf, kbase, gstart < k1 ? gstart : 0, u.L, col, grp);
-  bool first = true;
-  for (int g0 = gstart; g0 < k1; g0 += stride) {
-    V2Keys<T, D> kn;
-    const int gn = g0 + stride;
-    v2_load_keys<T, D>(kn, kbase, gn < k1 ? gn : g0, u.L, col, grp);
-    const bool full = g0 + kV2Group <= full_end;
-    if constexpr (ONLINE) {
-      if (full) v2_stats_group<T, D, true, 2>(p, u, qs, kf, g0, row_tiles, col, grp, mrow, zrow);
-      else v2_stats_group<T, D, false, 2>(p, u, qs, kf, g0, row_tiles, col, grp, mrow, zrow);
-    } else if (first) {
-      if (full) v2_stats_group<T, D, true, 0>(p, u, qs, kf, g0, row_tiles, col, grp, mrow, zrow);
-      else v2_stats_group<T, D, false, 0>(p, u, qs, kf, g0, row_tiles, col, grp, mrow, zrow);
+      if (next >= 0) load_keys<T, D>(kf, src, next);
     } else {
-      if (full) v2_stats_group<T, D, true, 1>(p, u, qs, kf, g0, row_tiles, col, grp, mrow, zrow);
-      else v2_stats_group<T, D, false, 1>(p, u, qs, kf, g0, row_tiles, col, grp, mrow, zrow);
+      float m, z[4];
+      int lim;
+      const auto begin = [&](int rt) {
+        m = mref[rt * kTileRows + l32];
+        z[0] = z[1] = z[2] = z[3] = 0.f;
+      };
+      const auto arg = [&](float x) { return fmaf(x, c, -m); };
+      const auto end_tile = [&](int rt) { acc[rt * kTileRows] += half_sum((z[0] + z[1]) + (z[2] + z[3])); };
+      if (g0 + C::group <= end) {
+        walk_rows<T, D>(kf, src, next, qrow, rt0, rw, tiles, begin, arg,
+                        [&](int, int i, float e) { z[i & 3] += e; }, end_tile);
+      } else {
+        walk_rows<T, D>(
+            kf, src, next, qrow, rt0, rw, tiles,
+            [&](int rt) {
+              begin(rt);
+              lim = last_visible(p, seg.L, r0 + rt * kTileRows + l32) - tile_key(g0, 0, half);
+            },
+            arg, [&](int kt, int i, float e) { z[i & 3] += tile_key(kt * 32, i, 0) <= lim ? e : 0.f; }, end_tile);
+      }
     }
-    first = false;
-    kf = kn;
   }
 }
 
-template <typename T, int D, int RTM>
-__global__ __launch_bounds__(kV2Threads, 1) void score_stats_v2_kernel(ScoreParams p) {
-  using C = V2Cfg<T, D, RTM>;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[C::q_bytes + C::merge_bytes];
+template <typename T, int D>
+__global__ __launch_bounds__(kThreads, 1) void score_stats_kernel(ScoreParams p) {
+  using C = ScoreCfg<T, D>;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[C::stats_lds];
   const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
-  const int col = lane & 15, grp = lane >> 4;
-  unsigned char *qs = smem;
-  V2Run run = v2_run(p, reinterpret_cast<long long *>(smem));
-  float *mrow_all = reinterpret_cast<float *>(smem + C::q_bytes);        // [wave][max_rows]
-  float *zrow_all = mrow_all + kV2Waves * C::max_rows;                   // [wave][max_rows]
-  float *mrow = mrow_all + wave * C::max_rows;
-  float *zrow = zrow_all + wave * C::max_rows;
-  const int row_tiles = (p.rows_pad / 16 + 1) & ~1;          // even; a pad tile is never reported
-  int sunit, sc0, sc1;
-  while (v2_next_segment(p, run, sunit, sc0, sc1)) {
-    const UnitInfo u = unit_info(p, sunit);
-    const int k0 = sc0 * p.chunk_keys;
-    const int k1 = min(u.L, sc1 * p.chunk_keys);
-    const T *kbase = reinterpret_cast<const T *>(p.k) + u.cunit * p.cap * D;
-    __syncthreads();                        // the previous segment's rows and partials are consumed
-    v2_stage_window<T, D, RTM>(p, u, qs);
-    for (int r = lane; r < C::max_rows; r += kWave) {   // a wave without keys reports empty rows
-      mrow[r] = -INFINITY;
-      zrow[r] = 0.f;
-    }
-    __syncthreads();
-    const int full_end = p.causal ? min(u.L, u.L - p.w + 1) : u.L;
-    const int g0 = k0 + wave * kV2Group;
-    v2_stats_keys<T, D, false>(p, u, qs, kbase, g0, k1, full_end, row_tiles, col, grp, mrow, zrow);
-    bool bad = false;
-    for (int r = lane; r < row_tiles * 16; r += kWave) bad |= !(zrow[r] <= 3.402823466e38f);
-    if (__any(bad)) {          // a sum overflowed against its reference: redo with a running maximum
-      for (int r = lane; r < row_tiles * 16; r += kWave) {
-        mrow[r] = -INFINITY;
-        zrow[r] = 0.f;
-      }
-      v2_stats_keys<T, D, true>(p, u, qs, kbase, g0, k1, full_end, row_tiles, col, grp, mrow, zrow);
-    }
-    __syncthreads();
-    // The segment's partial goes to its first chunk slot; its other slots are
-    // marked empty, so the row merge reads every slot it covers.
-    const int n_out = (sc1 - sc0) * p.rows_pad;
-    for (int i = threadIdx.x; i < n_out; i += kV2Threads) {
-      const int cs = sc0 + i / p.rows_pad;
-      const int r = i - (cs - sc0) * p.rows_pad;
-      float M = -INFINITY, Z = 0.f;
-      if (cs == sc0) {
-#pragma unroll
-        for (int w = 0; w < kV2Waves; ++w) M = fmaxf(M, mrow_all[w * C::max_rows + r]);
-        if (M != -INFINITY) {
-#pragma unroll
-          for (int w = 0; w < kV2Waves; ++w) {
-            const float mw = mrow_all[w * C::max_rows + r];
-            if (mw != -INFINITY) Z += zrow_all[w * C::max_rows + r] * fast_exp2(mw - M);
-          }
+  const int wave = uniform(static_cast<int>(threadIdx.x) / kWave);
+  const int l32 = lane & 31, half = lane >> 5;
+  float *sums = reinterpret_cast<float *>(smem + C::q_bytes);              // [wave][max_rows]
+  float *mref = reinterpret_cast<float *>(smem + C::q_bytes + C::sum_bytes);  // [max_rows]
+  float *acc = sums + wave * C::max_rows + l32;    // both halves of a row write the same value
+  const unsigned char *qrow = smem + l32 * C::q_stride + half * 16;
+  const int btiles = block_tiles<T, D>(p);
+  Share share = find_share(p, reinterpret_cast<long long *>(smem));
+  Segment seg;
+  while (next_segment(p, share, seg)) {
+    const KeySource src = key_source<T, D>(p, seg, l32, half);
+    float *part = p.row_part + static_cast<size_t>(share.b + seg.unit) * p.rows_pad * 2;
+    for (int r0 = 0; r0 < p.rows; r0 += btiles * kTileRows) {
+      const int tiles = min(btiles, (p.rows - r0 + kTileRows - 1) / kTileRows);
+      __syncthreads();                             // the previous rows and sums are consumed
+      stage_rows<T, D>(p, seg, smem, r0, tiles);
+      for (int rt = 0; rt < tiles; ++rt) acc[rt * kTileRows] = 0.f;
+      __syncthreads();
+      // References from the segment's first 32 keys, the row tiles dealt to the waves.
+      if (wave < tiles) {
+        Keys<T, D> kf;
+        load_key_tile<T, D>(kf.k[0], src, seg.k0);
+        for (int rt = wave; rt < tiles; rt += kWaves) {
+          Rows<T, D> r;
+          load_rows<T, D>(r, qrow, rt);
+          const f32x16_t s = tile_products<T, D>(kf.k[0], r);
+          const int lim = last_visible(p, seg.L, r0 + rt * kTileRows + l32);
+          const float m = half_max(tile_max(p, s, seg.k0, lim, half));
+          if (half == 0) mref[rt * kTileRows + l32] = m;
         }
       }
-      float *dst = p.row_part + ((u.ounit * p.chunks + cs) * p.rows_pad + r) * 2;
-      dst[0] = M;
-      dst[1] = Z;
+      __syncthreads();
+      const int rw = row_waves<T, D>(seg, tiles);
+      stats_groups<T, D, false>(p, seg, src, qrow, mref, acc, r0, tiles, wave, rw);
+      bool bad = false;
+      for (int rt = 0; rt < tiles; ++rt) bad |= !(acc[rt * kTileRows] <= 3.402823466e38f);
+      if (__syncthreads_or(bad)) {                 // a sum overflowed against its reference
+        for (int rt = 0; rt < tiles; ++rt) acc[rt * kTileRows] = -INFINITY;
+        stats_groups<T, D, true>(p, seg, src, qrow, mref, acc, r0, tiles, wave, rw);
+        __syncthreads();
+        for (int r = thread_id(); r < tiles * kTileRows; r += kThreads) {
+          float m = -INFINITY;
+#pragma unroll
+          for (int w = 0; w < kWaves; ++w) m = fmaxf(m, sums[w * C::max_rows + r]);
+          mref[r] = m;
+        }
+        __syncthreads();
+        for (int rt = 0; rt < tiles; ++rt) acc[rt * kTileRows] = 0.f;
+        stats_groups<T, D, false>(p, seg, src, qrow, mref, acc, r0, tiles, wave, rw);
+        __syncthreads();
+      }
+      for (int r = thread_id(); r < tiles * kTileRows && r0 + r < p.rows; r += kThreads) {
+        float z = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) z += sums[w * C::max_rows + r];
+        *reinterpret_cast<float2 *>(part + (r0 + r) * 2) = make_float2(mref[r], z);
+      }
     }
   }
 }
 
-// One resident workgroup per CU (the LDS of one holds the window rows).
-inline int v2_grid(const ScoreParams &p, int units) {
-  const long long n_items = static_cast<long long>(units) * p.chunks;   // at least the non-empty chunks
-  return static_cast<int>(n_items < p.cus ? n_items : p.cus);
-}
+// ---------------------------------------------------------------------------
+// Mass pass.
+// ---------------------------------------------------------------------------
 
-template <typename T, int D, int RTM>
-hipError_t launch_v2(ScoreParams p, int units, hipStream_t s) {
-  hipError_t e;
-  if (p.given) {
-    hipLaunchKernelGGL(score_given_stats_kernel, dim3((p.rows_pad + kThreads - 1) / kThreads, units), dim3(kThreads),
-                       0, s, p);
-  } else {
-    hipLaunchKernelGGL((score_stats_v2_kernel<T, D, RTM>), dim3(v2_grid(p, units)), dim3(kV2Threads), 0, s, p);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(score_rowmerge_kernel, dim3((p.rows_pad + kThreads - 1) / kThreads, units), dim3(kThreads), 0,
-                       s, p);
+// The workgroups whose shares hold chunks of the segment's unit, in order.  The
+// share of chunk c is the last one that begins at or before it, ceil((c + 1) *
+// grid / total) - 1.  With at least one chunk per share these are consecutive;
+// with fewer, each chunk has a workgroup of its own and some have none.
+struct UnitShares {
+  int n;           // how many
+  int first;       // dense: the first one
+  int chunk0, total, grid;
+
+  __device__ UnitShares(const ScoreParams &p, const Share &s, const Segment &seg) {
+    grid = static_cast<int>(gridDim.x);
+    const int nc = (seg.L + p.chunk_keys - 1) / p.chunk_keys;
+    total = 0;
+    if (s.total >= grid) {
+      first = static_cast<int>(((seg.before + 1) * grid + s.total - 1) / s.total) - 1;
+      n = static_cast<int>(((seg.before + nc) * grid + s.total - 1) / s.total) - first;
+    } else {
+      total = static_cast<int>(s.total);
+      chunk0 = static_cast<int>(seg.before);
+      n = nc;
+    }
   }
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((score_mass_v2_kernel<T, D, RTM>), dim3(v2_grid(p, units)), dim3(kV2Threads), 0, s, p);
-  return hipGetLastError();
+  __device__ __forceinline__ int workgroup(int i) const {
+    return total == 0 ? first + i : ((chunk0 + i + 1) * grid + total - 1) / total - 1;
+  }
+};
+
+// (max, 1/sum) of row r of the segment's unit, from the statistics partials
+// of the unit's segments or the decode statistics; absent or empty rows get
+// (+inf, 0), so that they add exactly zero.
+__device__ __forceinline__ float2 row_norm(const ScoreParams &p, const Segment &seg, const UnitShares &u, int r) {
+  const bool valid = r < p.rows && (seg.L >= p.w || seg.L - p.w + r % p.w >= 0);
+  float2 n = make_float2(INFINITY, 0.f);
+  if (!valid) return n;
+  if (p.given) {
+    const float *st = p.given + (static_cast<size_t>(seg.unit) * p.rows + r) * 2;
+    const float m = st[0], z = st[1];
+    if (m != -INFINITY && m != INFINITY && z > 0.f) n = make_float2(m, 1.f / z);
+    return n;
+  }
+  const float *part = p.row_part + (static_cast<size_t>(seg.unit) * p.rows_pad + r) * 2;
+  constexpr int kBatch = 8;                        // partials requested at once
+  float M = -INFINITY;
+  double Z = 0.0;
+  for (int s0 = 0; s0 < u.n; s0 += kBatch) {
+    float m[kBatch], z[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const float *st = part + static_cast<size_t>(u.workgroup(min(s0 + j, u.n - 1))) * p.rows_pad * 2;
+      m[j] = st[0];
+      z[j] = st[1];
+    }
+    float mb = M;
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) mb = s0 + j < u.n ? fmaxf(mb, m[j]) : mb;
+    if (mb == -INFINITY) continue;
+    Z *= static_cast<double>(fast_exp2(M - mb));
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j)
+      if (s0 + j < u.n && m[j] != -INFINITY)
+        Z += static_cast<double>(z[j]) * static_cast<double>(fast_exp2(m[j] - mb));
+    M = mb;
+  }
+  if (M != -INFINITY && Z > 0.0) n = make_float2(M, static_cast<float>(1.0 / Z));
+  return n;
 }
 
-// Row tiles the key-split kernels are built for, and whether the window rows
-// and their normalisers fit the LDS of one CU at that size.
-template <typename T, int D, int RTM>
-constexpr bool v2_fits() {
-  // fp32 at head_dim 128 needs 128 registers per key group and spills: the
-  // row-split kernels serve it.
-  return V2Cfg<T, D, RTM>::lds_bytes <= 160 * 1024 && !(sizeof(T) == 4 && D == 128);
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, 0xf, 0xf, true));
+}
+
+// Sum over the 32 lanes of each half, of the 16 * KT registers of a group:
+// each step halves the registers and folds one bit of the register index into
+// the lane index, so the lane ends with the total of one key (KT = 2), or the
+// lane pairs l, l ^ 16 with the same key's (KT = 1).  The lane partner of a
+// step differs in the step's bit (and may differ in lower ones, which are
+// summed over later).
+template <int KT>
+__device__ __forceinline__ float fold_keys(float (&a)[KT * 16], int lane) {
+  constexpr int kRor8 = 0x128, kHalfMirror = 0x141, kXor2 = 0x4e, kXor1 = 0xb1;
+  float b[16];
+  if constexpr (KT == 2) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {               // key tile <-> lane bit 4
+      const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a[i]), __float_as_uint(a[16 + i]), false, false);
+      b[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a[i]), __float_as_uint(a[i]), false, false);
+      b[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {                  // register bit 3 <-> lane bit 3
+    const float own = (lane & 8) ? b[8 + i] : b[i], other = (lane & 8) ? b[i] : b[8 + i];
+    b[i] = own + dpp<kRor8>(other);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {                  // register bit 2 <-> lane bit 2
+    const float own = (lane & 4) ? b[4 + i] : b[i], other = (lane & 4) ? b[i] : b[4 + i];
+    b[i] = own + dpp<kHalfMirror>(other);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {                  // register bit 1 <-> lane bit 1
+    const float own = (lane & 2) ? b[2 + i] : b[i], other = (lane & 2) ? b[i] : b[2 + i];
+    b[i] = own + dpp<kXor2>(other);
+  }
+  const float own = (lane & 1) ? b[1] : b[0], other = (lane & 1) ? b[0] : b[1];
+  return own + dpp<kXor1>(other);
+}
+
+// Key of the group that fold_keys leaves in `lane`.
+template <int KT>
+__device__ __forceinline__ int folded_key(int lane) {
+  return (KT == 2 ? (lane & 16) * 2 : 0) + ((lane & 8) << 1) + ((lane & 4) << 1) + ((lane & 32) >> 3) + (lane & 3);
+}
+
+// The score of `key` over the row block at r0.  With several blocks the sums
+// are added with what each addition rounds off kept aside (in `lost`, by key
+// of the segment) and added last, so that the number of blocks costs no
+// precision.
+__device__ __forceinline__ void add_block(const ScoreParams &p, float *out, float *lost, const Segment &seg, int r0,
+                                          int btiles, int key, float tot) {
+  if (r0 == 0) {
+    out[key] = tot;
+    if (p.rows > btiles * kTileRows) lost[key - seg.k0] = 0.f;
+    return;
+  }
+  const float a = out[key], s = a + tot;
+  const float b = s - a;
+  const float e = lost[key - seg.k0] + ((a - (s - b)) + (tot - b));
+  const bool last = r0 + btiles * kTileRows >= p.rows;
+  out[key] = last ? s + e : s;
+  lost[key - seg.k0] = e;
 }
 
 template <typename T, int D>
-hipError_t try_launch_v2(const ScoreParams &p0, hipStream_t s, bool &done) {
-  done = false;
-  const int units = p0.n_layers * p0.batch * p0.hkv;
-  const int row_tiles = p0.rows_pad / 16;
+__global__ __launch_bounds__(kThreads, 1) void score_mass_kernel(ScoreParams p) {
+  using C = ScoreCfg<T, D>;
+  constexpr int KT = C::KT;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[C::mass_lds];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = uniform(static_cast<int>(threadIdx.x) / kWave);
+  const int l32 = lane & 31, half = lane >> 5;
+  float2 *norm = reinterpret_cast<float2 *>(smem + C::q_bytes);            // [max_rows] (max, 1/sum)
+  const unsigned char *qrow = smem + l32 * C::q_stride + half * 16;
+  __shared__ int s_next;
+  __shared__ float part[kWaves][kWave];
+  __shared__ float lost[C::lost_keys];
+  const float c = p.scale_log2;
+  const int btiles = block_tiles<T, D>(p);
+  Share share = find_share(p, reinterpret_cast<long long *>(smem));
+  Segment seg;
+  const bool blocks = p.rows > btiles * kTileRows;
+  while (next_segment(p, share, seg, blocks ? C::lost_keys : 1 << 30)) {
+    const KeySource src = key_source<T, D>(p, seg, l32, half);
+    float *out = p.scores + static_cast<size_t>(seg.unit) * p.cap;
+    const int end = full_end(p, seg.L);
+    const UnitShares shares(p, share, seg);
+    for (int r0 = 0; r0 < p.rows; r0 += btiles * kTileRows) {
+      const int tiles = min(btiles, (p.rows - r0 + kTileRows - 1) / kTileRows);
+      const int rw = row_waves<T, D>(seg, tiles);
+      int g0 = seg.k0 + wave / rw * C::group;
+      Keys<T, D> kf;
+      load_keys<T, D>(kf, src, g0 < seg.k1 ? g0 : seg.k0);
+      __syncthreads();                             // every wave is done with the previous rows
+      if (threadIdx.x == 0) s_next = kWaves;
+      stage_rows<T, D>(p, seg, smem, r0, tiles);
+      for (int r = thread_id(); r < tiles * kTileRows; r += kThreads)
+        norm[r] = row_norm(p, seg, shares, r0 + r);
+      __syncthreads();
+      // The older wave of a SIMD wins most issue slots and would finish a fixed
+      // share early, so the groups after the first are taken from a counter
+      // (which wave computes a score does not change it).
+      int next;
+      for (; g0 >= 0 && g0 < seg.k1; g0 = next) {
+        next = -1;
+        if (rw == 1) {
+          int taken = 0;
+          if (lane == 0) taken = atomicAdd(&s_next, 1);
+          const int g = seg.k0 + uniform(taken) * C::group;
+          if (g < seg.k1) next = g;
+        }
+        float acc[KT * 16];
+#pragma unroll
+        for (int i = 0; i < KT * 16; ++i) acc[i] = 0.f;
+        float2 n;
+        int lim;
+        const auto arg = [&](float x) { return fmaf(x, c, -n.x); };
+        if (g0 + C::group <= end) {
+          walk_rows<T, D>(
+              kf, src, next, qrow, wave % rw, rw, tiles, [&](int rt) { n = norm[rt * kTileRows + l32]; }, arg,
+              [&](int kt, int i, float e) { acc[kt * 16 + i] = fmaf(e, n.y, acc[kt * 16 + i]); }, [](int) {});
+        } else {
+          walk_rows<T, D>(
+              kf, src, next, qrow, wave % rw, rw, tiles,
+              [&](int rt) {
+                n = norm[rt * kTileRows + l32];
+                lim = last_visible(p, seg.L, r0 + rt * kTileRows + l32) - tile_key(g0, 0, half);
+              },
+              arg,
+              [&](int kt, int i, float e) {
+                acc[kt * 16 + i] = fmaf(tile_key(kt * 32, i, 0) <= lim ? e : 0.f, n.y, acc[kt * 16 + i]);
+              },
+              [](int) {});
+        }
+        const float tot = fold_keys<KT>(acc, lane);
+        const int key = g0 + folded_key<KT>(lane);
+        const bool mine = (KT == 2 || !(lane & 16)) && key < seg.k1;
+        if (rw == 1) {
+          if (mine) add_block(p, out, lost, seg, r0, btiles, key, tot);
+        } else {
+          part[wave][lane] = tot;                  // one group per wave: summed after the loop
+        }
+      }
+      if (rw > 1) {
+        __syncthreads();
+        const int key = seg.k0 + wave / rw * C::group + folded_key<KT>(lane);
+        if (wave % rw == 0 && (KT == 2 || !(lane & 16)) && key < seg.k1) {
+          float tot = part[wave][lane];
+          for (int i = 1; i < rw; ++i) tot += part[wave + i][lane];
+          add_block(p, out, lost, seg, r0, btiles, key, tot);
+        }
+      }
+    }
+  }
+}
+
+// Chunks are the unit of load balance over the persistent grid: 512 keys, one
+// 64-key group for each wave, when every CU gets many of them; else 64 keys,
+// so that mid-sized and small calls spread evenly over the CUs.  Units
+// of at most 512 keys stay whole when there is one for every CU: cutting them
+// would stage a unit's window rows more than once (480 units of 259 keys, 512
+// window rows: 143 us in 64-key chunks, 105 us whole, with one block of rows).
+void score_plan(ScoreParams &p, int units, int &grid) {
+  p.chunk_keys = kScoreChunk;
+  const bool whole_units = p.cap <= kScoreChunk && units >= p.cus;
+  if (!whole_units && static_cast<long long>(units) * ((p.cap + p.chunk_keys - 1) / p.chunk_keys) < 8LL * p.cus)
+    p.chunk_keys = 64;
+  const long long chunks = static_cast<long long>(units) * ((p.cap + p.chunk_keys - 1) / p.chunk_keys);
+  long long g = chunks < p.cus ? chunks : p.cus;
+  if (!p.given && g > p.part_slots - units + 1) g = p.part_slots - units + 1;   // a slot for every segment
+  grid = static_cast<int>(g);
+}
+
+template <typename T, int D>
+hipError_t launch_typed(const ScoreParams &p0, hipStream_t s) {
   ScoreParams p = p0;
-  // Keys per workgroup: 1024, or 2048 when that still gives every CU many workgroups.
-  // Chunks are the unit of load balance over the persistent grid: 512 keys
-  // when the call is small (a few chunks per CU would leave the shares
-  // uneven), 1024 otherwise (fewer per-chunk statistics for the row merge).
-  p.chunk_keys = 1024;
-  if (static_cast<long long>(units) * ((p.cap + 511) / 512) <= 64LL * p.cus) p.chunk_keys = 512;
-  p.chunks = (p.cap + p.chunk_keys - 1) / p.chunk_keys;
-  done = true;
-  if constexpr (v2_fits<T, D, 8>()) {
-    if (row_tiles <= 8) return launch_v2<T, D, 8>(p, units, s);
-  }
-  if constexpr (v2_fits<T, D, 16>()) {
-    if (row_tiles <= 16) return launch_v2<T, D, 16>(p, units, s);
-  }
-  if constexpr (v2_fits<T, D, 28>()) {
-    if (row_tiles <= 28) return launch_v2<T, D, 28>(p, units, s);
-  }
-  if constexpr (v2_fits<T, D, 34>()) {
-    if (row_tiles <= 34) return launch_v2<T, D, 34>(p, units, s);
-  }
-  done = false;
-  return hipSuccess;
-}
-
-template <typename T, int D, int RTW>
-hipError_t launch_rtw(const ScoreParams &p, int waves, hipStream_t s) {
-  const int units = p.n_layers * p.batch * p.hkv;
-  hipError_t e;
-  if (p.given) {
-    hipLaunchKernelGGL(score_given_stats_kernel, dim3((p.rows_pad + kThreads - 1) / kThreads, units), dim3(kThreads),
-                       0, s, p);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  } else {
-    hipLaunchKernelGGL((score_stats_kernel<T, D, RTW>), dim3(8 * p.chunks, (units + 7) / 8), dim3(waves * kWave), 0, s,
-                       p);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(score_rowmerge_kernel, dim3((p.rows_pad + kThreads - 1) / kThreads, units), dim3(kThreads), 0,
-                       s, p);
-    e = hipGetLastError();
+  int grid;
+  score_plan(p, p.n_layers * p.batch * p.hkv, grid);
+  if (!p.given) {
+    hipLaunchKernelGGL((score_stats_kernel<T, D>), dim3(grid), dim3(kThreads), 0, s, p);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((score_mass_kernel<T, D, RTW>), dim3(8 * p.chunks, (units + 7) / 8), dim3(waves * kWave), 0, s,
-                     p);
+  hipLaunchKernelGGL((score_mass_kernel<T, D>), dim3(grid), dim3(kThreads), 0, s, p);
   return hipGetLastError();
-}
-
-// Row tiles per wave: the four waves split the G * w window rows evenly, up
-// to eight 16-row tiles each (more rows loop over groups of 32 tiles).  Each
-// staged K fragment then feeds up to eight MFMA tiles; spreading the rows
-// over more waves (4 tiles each) measured 1.4x slower on the 7B window
-// (448 rows) despite the higher occupancy.
-template <typename T, int D>
-hipError_t launch_typed(const ScoreParams &p, hipStream_t s) {
-  bool done = false;
-  const hipError_t e2 = try_launch_v2<T, D>(p, s, done);
-  if (done) return e2;
-  const int row_tiles = p.rows_pad / 16;
-  switch ((row_tiles + kWaves - 1) / kWaves) {
-    case 1: return launch_rtw<T, D, 1>(p, kWaves, s);
-    case 2: return launch_rtw<T, D, 2>(p, kWaves, s);
-    case 3: return launch_rtw<T, D, 3>(p, kWaves, s);
-    case 4: return launch_rtw<T, D, 4>(p, kWaves, s);
-    case 5: return launch_rtw<T, D, 5>(p, kWaves, s);
-    case 6: return launch_rtw<T, D, 6>(p, kWaves, s);
-    case 7: return launch_rtw<T, D, 7>(p, kWaves, s);
-    default: return launch_rtw<T, D, 8>(p, kWaves, s);
-  }
 }
 
 }  // namespace
 
-size_t score_workspace_bytes(int units, int capacity, int rows) {
+size_t score_min_workspace_bytes(int units, int capacity, int rows) {
   const size_t rows_pad = static_cast<size_t>((rows + 15) / 16 * 16);
   const size_t chunks = static_cast<size_t>((capacity + kScoreChunk - 1) / kScoreChunk);
   return static_cast<size_t>(units) * rows_pad * (chunks + 1) * 2 * sizeof(float);
+}
+
+size_t score_workspace_bytes(int units, int capacity, int rows) {
+  const size_t rows_pad = static_cast<size_t>((rows + 15) / 16 * 16);
+  const size_t slots = (static_cast<size_t>(units) + kScoreMaxGrid) * rows_pad * 2 * sizeof(float);
+  const size_t least = score_min_workspace_bytes(units, capacity, rows);
+  return slots > least ? slots : least;
 }
 
 hipError_t launch_score(const ScoreParams &p, int dtype, int head_dim, hipStream_t s) {

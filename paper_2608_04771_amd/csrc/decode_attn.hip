@@ -11,10 +11,14 @@
 // The S^T accumulator already holds, per lane, the probabilities the P^T
 // operand needs (same lane, same element slot), so P never leaves registers.
 // K and V are streamed with coalesced non-temporal 16-byte loads (each 128-byte
-// line read whole, nothing allocated in L2) and staged through LDS: K is
-// re-read in the MFMA operand layout, V column-wise.  Softmax is online in the
-// log2 domain with fp32 statistics.  The four waves' (max, sum, O) states are
-// merged through LDS and written as one split partial.  A second kernel
+// line read whole, nothing allocated in L2) and staged through LDS, one after
+// the other through one buffer: K is re-read in the MFMA operand layout, V
+// column-wise.  Softmax is online in the log2 domain with fp32 statistics.
+// The waves' (max, sum, O) states are merged through LDS and written as one
+// split partial: every store and load of that merge is 16 bytes on a row pitch
+// free of bank conflicts (as 4-byte stores on a pitch of D, 16 lanes on one
+// bank, it took 2 us of each call: 28 one-layer calls 397 -> 359 us, 256 units
+// x 1,100 rows 27.8 -> 26.5 us, 112 units x 9,645 rows 88.2 -> 86.4 us).  A second kernel
 // merges the splits of each unit, writes out / lse and commits the optional
 // append (so no workgroup of the attention kernel races on len); a unit
 // covered by a single workgroup (one split) is finalised by that workgroup,
@@ -36,11 +40,9 @@ namespace reco {
 namespace {
 
 constexpr int kTile = kDecodeTile;   // keys per wave iteration
-constexpr int kWavesPerWG = 4;
-constexpr int kThreads = kWavesPerWG * kWave;
 constexpr int kMaxSplits = kDecodeMaxSplits;
 
-template <typename T, int D>
+template <typename T, int D, int NW = 4>
 struct DecodeCfg {
   using MF = Mfma<T>;
   static constexpr int kpl = MF::kPerLane;
@@ -51,9 +53,12 @@ struct DecodeCfg {
   static constexpr int row_bytes = D * (int)sizeof(T);
   static constexpr int lds_stride = row_bytes + 8;  // padded row pitch of the V stage
   static constexpr int k_stride = row_bytes + 16;   // padded, 16-byte aligned pitch of the K stage
-  static constexpr int wave_stage = kTile * (lds_stride + k_stride);
-  static constexpr int stage_bytes = kWavesPerWG * wave_stage;
-  static constexpr int merge_bytes = kWavesPerWG * (32 + 16 * D) * 4;
+  static constexpr int wave_stage = kTile * k_stride;   // K, then V of the same tile (a wave's LDS accesses run in order)
+  static constexpr int stage_bytes = NW * wave_stage;
+  // Cross-wave merge: a lane's four consecutive outputs are one 16-byte store,
+  // and the row pitch shifts the eight rows stored together over all banks.
+  static constexpr int merge_pitch = D + 4;
+  static constexpr int merge_bytes = NW * 16 * (2 + merge_pitch) * 4;
   static constexpr int smem_bytes = stage_bytes > merge_bytes ? stage_bytes : merge_bytes;
   // Coalesced tile loads: per instruction the wave reads 1 KB of consecutive
   // rows (lane l takes 16 bytes at l * 16), so every 128-byte line is read whole.
@@ -62,7 +67,7 @@ struct DecodeCfg {
   static constexpr int v_insts = kTile / rows_per_inst;
   // Two workgroups per CU (two waves per SIMD) where the double-buffered
   // tile fits in 256 registers; the fp32 head_dim-128 variant needs more.
-  static constexpr int min_wgs = (sizeof(T) == 4 && D == 128) ? 1 : 2;
+  static constexpr int min_wgs = (sizeof(T) == 4 && D == 128) || NW == 8 ? 1 : 2;
 };
 
 // Registers of one 32-key tile: K and V as coalesced 16-byte pieces bound
@@ -147,9 +152,10 @@ __device__ __forceinline__ typename Mfma<T>::frag pt_frag(const float (&pv)[8], 
   }
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(kThreads, (DecodeCfg<T, D>::min_wgs)) void decode_split_kernel(DecodeParams p) {
-  using Cfg = DecodeCfg<T, D>;
+template <typename T, int D, int NW>
+__global__ __launch_bounds__(NW * kWave, (DecodeCfg<T, D, NW>::min_wgs)) void decode_split_kernel(DecodeParams p) {
+  using Cfg = DecodeCfg<T, D, NW>;
+  constexpr int kThreads = NW * kWave;
   using MF = Mfma<T>;
   using frag = typename MF::frag;
   __shared__ __attribute__((aligned(16))) unsigned char smem[Cfg::smem_bytes];
@@ -198,16 +204,16 @@ __global__ __launch_bounds__(kThreads, (DecodeCfg<T, D>::min_wgs)) void decode_s
   for (int dt = 0; dt < Cfg::dtiles; ++dt) o[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   unsigned char *stage = smem + wave * Cfg::wave_stage;           // V, row pitch lds_stride
-  unsigned char *kstage = stage + kTile * Cfg::lds_stride;          // K, row pitch k_stride
+  unsigned char *kstage = stage;                                    // K, row pitch k_stride
 
   TileRegs<T, D> cur;
   if (t0 + wave < t1) load_tile<T, D>(cur, (t0 + wave) * kTile, n_cache, append, kbase, vbase, knew, vnew, lane);
-  for (int t = t0 + wave; t < t1; t += kWavesPerWG) {
+  for (int t = t0 + wave; t < t1; t += NW) {
     const int kb = t * kTile;
     // Prefetch this wave's next tile (the last iteration re-reads its own
     // tile, which stays cached) so loads are in flight during the compute.
     TileRegs<T, D> nxt;
-    const int tn = min(t + kWavesPerWG, t1 - 1);
+    const int tn = min(t + NW, t1 - 1);
     load_tile<T, D>(nxt, tn * kTile, n_cache, append, kbase, vbase, knew, vnew, lane);
     // K tile -> LDS -> MFMA operand layout (lane holds key hf*16 + col,
     // head-dim slice grp*dq + c*kpl of it).
@@ -290,42 +296,57 @@ __global__ __launch_bounds__(kThreads, (DecodeCfg<T, D>::min_wgs)) void decode_s
 
   // Cross-wave merge through LDS.
   __syncthreads();
-  float *mw = reinterpret_cast<float *>(smem);   // [4][16]
-  float *lw = mw + kWavesPerWG * 16;             // [4][16]
-  float *ow = lw + kWavesPerWG * 16;             // [4][16][D]
+  float *mw = reinterpret_cast<float *>(smem);   // [NW][16]
+  float *lw = mw + NW * 16;                      // [NW][16]
+  float *ow = lw + NW * 16;                      // [NW][16][merge_pitch]
   if (grp == 0) {
     mw[wave * 16 + col] = m_run;
     lw[wave * 16 + col] = l_tot;
   }
 #pragma unroll
-  for (int dt = 0; dt < Cfg::dtiles; ++dt) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) ow[(wave * 16 + col) * D + dt * 16 + 4 * grp + i] = o[dt][i];
-  }
+  for (int dt = 0; dt < Cfg::dtiles; ++dt)
+    *reinterpret_cast<float4 *>(ow + (wave * 16 + col) * Cfg::merge_pitch + dt * 16 + 4 * grp) =
+        make_float4(o[dt][0], o[dt][1], o[dt][2], o[dt][3]);
   __syncthreads();
+  // Four outputs d .. d + 3 of query qi over all waves, with the maximum M and
+  // the sum L of the workgroup's softmax.
+  const auto merged = [&](int qi, int d, float &M, float &L) {
+    M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, mw[w * 16 + qi]);
+    L = 0.f;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (M != -INFINITY) {
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const float e = fast_exp2(mw[w * 16 + qi] - M);
+        const float4 x = *reinterpret_cast<const float4 *>(ow + (w * 16 + qi) * Cfg::merge_pitch + d);
+        acc.x += x.x * e;
+        acc.y += x.y * e;
+        acc.z += x.z * e;
+        acc.w += x.w * e;
+        L += lw[w * 16 + qi] * e;
+      }
+    }
+    return acc;
+  };
 
   if (p.splits == 1) {
     // The workgroup holds its unit's whole softmax: it writes out / lse /
     // row_stats and commits the append itself, with the arithmetic of the
     // merge of a single split (weight exp2(0) * 1/L, added to zero).
     const size_t oq0 = (static_cast<size_t>(lc) * p.batch + b) * p.hq + h * p.group;
-    for (int idx = threadIdx.x; idx < p.group * D; idx += kThreads) {
-      const int qi = idx / D;
-      const int d = idx - qi * D;
-      float M = -INFINITY;
-#pragma unroll
-      for (int w = 0; w < kWavesPerWG; ++w) M = fmaxf(M, mw[w * 16 + qi]);
-      float acc = 0.f, L = 0.f;
-      if (M != -INFINITY) {
-#pragma unroll
-        for (int w = 0; w < kWavesPerWG; ++w) {
-          const float e = fast_exp2(mw[w * 16 + qi] - M);
-          acc += ow[(w * 16 + qi) * D + d] * e;
-          L += lw[w * 16 + qi] * e;
-        }
-      }
+    for (int idx = threadIdx.x; idx < p.group * (D / 4); idx += kThreads) {
+      const int qi = idx / (D / 4);
+      const int d = (idx - qi * (D / 4)) * 4;
+      float M, L;
+      const float4 acc = merged(qi, d, M, L);
       const float inv = L > 0.f ? 1.f / L : 0.f;
-      reinterpret_cast<T *>(p.out)[(oq0 + qi) * D + d] = from_f32<T>(fmaf(acc, inv, 0.f));
+      T *dst = reinterpret_cast<T *>(p.out) + (oq0 + qi) * D + d;
+      dst[0] = from_f32<T>(fmaf(acc.x, inv, 0.f));
+      dst[1] = from_f32<T>(fmaf(acc.y, inv, 0.f));
+      dst[2] = from_f32<T>(fmaf(acc.z, inv, 0.f));
+      dst[3] = from_f32<T>(fmaf(acc.w, inv, 0.f));
       if (d == 0) {
         if (p.lse) p.lse[oq0 + qi] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
         if (p.row_stats) {
@@ -353,29 +374,21 @@ __global__ __launch_bounds__(kThreads, (DecodeCfg<T, D>::min_wgs)) void decode_s
   const size_t pbase = static_cast<size_t>(unit) * p.splits + split;
   float *po = p.part_o + pbase * 16 * D;
   float *pml = p.part_ml + pbase * 32;
-  for (int idx = threadIdx.x; idx < p.group * D; idx += kThreads) {
-    const int qi = idx / D;
-    const int d = idx - qi * D;
-    float M = -INFINITY;
-#pragma unroll
-    for (int w = 0; w < kWavesPerWG; ++w) M = fmaxf(M, mw[w * 16 + qi]);
-    float acc = 0.f;
-    if (M != -INFINITY) {
-#pragma unroll
-      for (int w = 0; w < kWavesPerWG; ++w) acc += ow[(w * 16 + qi) * D + d] * fast_exp2(mw[w * 16 + qi] - M);
-    }
-    po[qi * D + d] = acc;
+  for (int idx = threadIdx.x; idx < p.group * (D / 4); idx += kThreads) {
+    const int qi = idx / (D / 4);
+    const int d = (idx - qi * (D / 4)) * 4;
+    float M, L;
+    const float4 acc = merged(qi, d, M, L);
+    float *dst = po + qi * D + d;
+    dst[0] = acc.x;
+    dst[1] = acc.y;
+    dst[2] = acc.z;
+    dst[3] = acc.w;
     if (d == 0) {
-      float L = 0.f;
-      if (M != -INFINITY) {
-#pragma unroll
-        for (int w = 0; w < kWavesPerWG; ++w) L += lw[w * 16 + qi] * fast_exp2(mw[w * 16 + qi] - M);
-      }
       pml[qi] = M;
       pml[16 + qi] = L;
     }
   }
-
 }
 
 // Merge the split partials of every (unit, query head), write out / lse and
@@ -593,7 +606,16 @@ __global__ __launch_bounds__(kWideThreads) void decode_merge_wide_kernel(DecodeP
 template <typename T, int D>
 hipError_t launch_typed(const DecodeParams &p, hipStream_t s) {
   const int units = p.n_layers * p.batch * p.hkv;
-  hipLaunchKernelGGL((decode_split_kernel<T, D>), dim3(p.splits, units), dim3(kThreads), 0, s, p);
+  // Eight waves where a split holds more tiles than four waves take in one
+  // round and nothing else hides the second round: small calls of long units
+  // (28 one-layer calls of 4 units x 9,645 rows: 352 us against 359 us).  With
+  // few splits per unit (longer runs of tiles) eight waves only add to the
+  // merge (112 units x 9,645 rows: 88.4 us against 86.4 us).
+  const int tiles_cap = (p.cap + 1 + kTile - 1) / kTile;
+  if (p.splits >= kWideMinSplits && tiles_cap >= 6 * p.splits)
+    hipLaunchKernelGGL((decode_split_kernel<T, D, 8>), dim3(p.splits, units), dim3(8 * kWave), 0, s, p);
+  else
+    hipLaunchKernelGGL((decode_split_kernel<T, D, 4>), dim3(p.splits, units), dim3(4 * kWave), 0, s, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.splits == 1) return e;   // one split: finalised in place
   if (p.splits >= kWideMinSplits)

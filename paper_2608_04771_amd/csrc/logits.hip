@@ -46,13 +46,20 @@ __global__ __launch_bounds__(kPenThreads) void logit_penalty_kernel(float *logit
 // penalty does), and the next token is the argmax of z~ (T = 0) or, for
 // T > 0, the Gumbel-max draw argmax(z~ / T + G), which is an exact sample of
 // softmax(z~ / T).  G = -log(-log U) with U from Philox4x32-10.  Workgroups
-// take 1024-element chunks of a row (one Philox block of four per thread) and
-// leave (best value, index) partials; a one-wave-per-row kernel merges them.  Ties and equal partials go to the
-// lowest index; NaN values never win.
+// take chunks of a row (one Philox block of four logits per thread and round)
+// and leave (best value, index) partials; a one-wave-per-row kernel merges
+// them.  Ties and equal partials go to the lowest index; NaN values never win.
+//
+// Bound by VALU issue: per logit the Philox rounds, two logarithms and a
+// division.  Only one logit of a chunk can win, so calls of many chunks bound
+// every value from two bare v_log_f32 first and compute y as defined only
+// where it can reach the chunk's maximum (256 rows x 152,064:
+// 83.9 us with every value computed, 43.9 us).
 
 constexpr int kSmpThreads = 256;
-constexpr int kSmpChunk = kSmpThreads * 4;   // logits per workgroup: one Philox block of 4 per thread
-constexpr int kSmpBitWords = kSmpChunk / 32;
+constexpr int kSmpRound = kSmpThreads * 4;   // logits a workgroup takes at once: one Philox block of 4 per thread
+constexpr int kSmpRounds = 4;                // rounds of a workgroup in calls of many chunks
+constexpr int64_t kSmpWideMin = 2048;        // chunks of one round from which a call has many
 
 // Philox4x32 with 10 rounds (Salmon, Moraes, Dror and Shaw, SC 2011): each
 // round multiplies counter words 0 and 2 by the two round constants, crosses
@@ -61,9 +68,11 @@ constexpr int kSmpBitWords = kSmpChunk / 32;
 __device__ __forceinline__ void philox4x32_10(uint32_t (&c)[4], uint32_t k0, uint32_t k1) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    const uint32_t a = c[0], b = c[2];
-    const uint32_t lo0 = 0xD2511F53u * a, hi0 = __umulhi(0xD2511F53u, a);
-    const uint32_t lo1 = 0xCD9E8D57u * b, hi1 = __umulhi(0xCD9E8D57u, b);
+    // 64-bit products: one v_mad_u64_u32 instead of a v_mul_lo and a v_mul_hi
+    const uint64_t p0 = static_cast<uint64_t>(0xD2511F53u) * c[0];
+    const uint64_t p1 = static_cast<uint64_t>(0xCD9E8D57u) * c[2];
+    const uint32_t lo0 = static_cast<uint32_t>(p0), hi0 = static_cast<uint32_t>(p0 >> 32);
+    const uint32_t lo1 = static_cast<uint32_t>(p1), hi1 = static_cast<uint32_t>(p1 >> 32);
     c[0] = hi1 ^ c[1] ^ k0;
     c[1] = lo1;
     c[2] = hi0 ^ c[3] ^ k1;
@@ -99,25 +108,62 @@ struct SamplePart {
   int32_t i;
 };
 
+// The value a logit enters the draw with (T > 0).
+__device__ __forceinline__ float gumbel_value(float x, float temperature, uint32_t bits) {
+  const float g = -logf(-logf(unit_open(bits)));
+  return x / temperature + g;
+}
+
+// ROUNDS > 1 takes only T in [kFilterMinT, kFilterMaxT], where x * (1 / T)
+// is x / T to 2 ulp or overflows with it.
+constexpr float kFilterMinT = 1e-30f;
+constexpr float kFilterMaxT = 1e30f;
+
+// The largest y of a chunk whose largest estimate is `a` has an estimate no
+// smaller than this.  Estimate and y differ by a constant (log ln 2) and by
+// less than 2e-5 + 4e-7 |x / T|: the two forms of G differ by at most 1.6e-6
+// over all 2^23 uniforms (measured), the rest is the rounding of x / T and of
+// the sum; |G| < 17, so |x / T| < |a| + 18 where the estimate is near a.
+// NaN for an infinite a: every comparison with it lets the exact value decide.
+__device__ __forceinline__ float filter_floor(float a) { return a - (2e-4f + 4e-6f * fabsf(a)); }
+
+template <int ROUNDS, bool VEC>
 __global__ __launch_bounds__(kSmpThreads) void penalty_sample_partial_kernel(
     float *logits, int vocab, int64_t ld, const int32_t *ids, int n_ids, const float *reward, float tau_lo,
     float tau_hi, float b_lo, float b_mid, float b_hi, float temperature, uint32_t seed_lo, uint32_t seed_hi,
     uint32_t off_lo, uint32_t off_hi, int chunks, SamplePart *part, int32_t *dev_err) {
-  __shared__ uint32_t s_bits[kSmpBitWords];
-  __shared__ SamplePart s_red[kSmpThreads / kWave];
+  constexpr int kChunk = ROUNDS * kSmpRound;
+  constexpr int kBitWords = kChunk / 32;
+  constexpr int kWaves = kSmpThreads / kWave;
+  __shared__ uint32_t s_bits[kBitWords];
+  __shared__ SamplePart s_red[kWaves];
+  __shared__ float s_top[kWaves];
   const int chunk = blockIdx.x;
   const int row = blockIdx.y;
-  const int c0 = chunk * kSmpChunk;
-  const int r0 = threadIdx.x * 4;                    // chunk-relative, multiple of 4
-  const int j0 = c0 + r0;
+  const int c0 = chunk * kChunk;
+  const int r0 = threadIdx.x * 4;                    // round-relative, multiple of 4
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = threadIdx.x / kWave;
   float *z = logits + static_cast<int64_t>(row) * ld;
   // Issue every global load before the first barrier so their latencies overlap.
-  float x[4];
+  float x[ROUNDS][4];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) x[e] = (j0 + e < vocab) ? z[j0 + e] : -INFINITY;
+  for (int t = 0; t < ROUNDS; ++t) {
+    const int j0 = c0 + t * kSmpRound + r0;
+    if (VEC && j0 + 3 < vocab) {
+      const float4 u = *reinterpret_cast<const float4 *>(z + j0);
+      x[t][0] = u.x;
+      x[t][1] = u.y;
+      x[t][2] = u.z;
+      x[t][3] = u.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[t][e] = (j0 + e < vocab) ? z[j0 + e] : -INFINITY;
+    }
+  }
   const float v = reward[row];
   const int my_id = (static_cast<int>(threadIdx.x) < n_ids) ? ids[threadIdx.x] : -1;
-  if (threadIdx.x < kSmpBitWords) s_bits[threadIdx.x] = 0u;
+  if (threadIdx.x < kBitWords) s_bits[threadIdx.x] = 0u;
   __syncthreads();
   // Mark the reflection ids that fall in this chunk; a set, so duplicates merge.
   for (int i = threadIdx.x; i < n_ids; i += kSmpThreads) {
@@ -127,45 +173,107 @@ __global__ __launch_bounds__(kSmpThreads) void penalty_sample_partial_kernel(
       continue;
     }
     const int r = u - c0;
-    if (r >= 0 && r < kSmpChunk) atomicOr(&s_bits[r >> 5], 1u << (r & 31));
+    if (r >= 0 && r < kChunk) atomicOr(&s_bits[r >> 5], 1u << (r & 31));
   }
   __syncthreads();
   const float beta = (v <= tau_lo) ? b_lo : ((v >= tau_hi) ? b_hi : b_mid);   // Eq. 3 as written
+#pragma unroll
+  for (int t = 0; t < ROUNDS; ++t) {
+    const int r = t * kSmpRound + r0;
+    const uint32_t bits = (s_bits[r >> 5] >> (r & 31)) & 0xFu;   // ids are inside the row
+    if (bits) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if ((bits >> e) & 1u) {                      // Eq. 4, one fp32 subtraction
+          x[t][e] = x[t][e] - beta;
+          z[c0 + r + e] = x[t][e];
+        }
+    }
+  }
 
   float best = -INFINITY;
   int best_i = 0x7fffffff;
-  if (j0 < vocab) {
-    const uint32_t bits = (s_bits[r0 >> 5] >> (r0 & 31)) & 0xFu;
+  const auto draw = [&](int j0, uint32_t (&c)[4]) {
+    c[0] = static_cast<uint32_t>(j0 >> 2);
+    c[1] = static_cast<uint32_t>(row);
+    c[2] = off_lo;
+    c[3] = off_hi;
+    philox4x32_10(c, seed_lo, seed_hi);
+  };
+  if (temperature == 0.f) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if ((bits >> e) & 1u) {                        // Eq. 4, one fp32 subtraction
-        x[e] = x[e] - beta;
-        z[j0 + e] = x[e];
-      }
-    if (temperature == 0.f) {
+    for (int t = 0; t < ROUNDS; ++t) {
+      const int j0 = c0 + t * kSmpRound + r0;
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        if (j0 + e < vocab) arg_better(best, best_i, x[e], j0 + e);
-    } else {
-      uint32_t c[4] = {static_cast<uint32_t>(j0 >> 2), static_cast<uint32_t>(row), off_lo, off_hi};
-      philox4x32_10(c, seed_lo, seed_hi);
+        if (j0 + e < vocab) arg_better(best, best_i, x[t][e], j0 + e);
+    }
+  } else if constexpr (ROUNDS == 1) {
+    const int j0 = c0 + r0;
+    if (j0 < vocab) {
+      uint32_t c[4];
+      draw(j0, c);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float g = -logf(-logf(unit_open(c[e])));
-        const float y = x[e] / temperature + g;
+        const float y = gumbel_value(x[0][e], temperature, c[e]);
         if (j0 + e < vocab) arg_better(best, best_i, y, j0 + e);
+      }
+    }
+  } else {
+    // Estimates of y - log ln 2, the largest of each thread and round kept.
+    const float inv_t = 1.f / temperature;
+    float top[ROUNDS];
+    float a = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < ROUNDS; ++t) {
+      const int j0 = c0 + t * kSmpRound + r0;
+      uint32_t c[4];
+      draw(j0, c);
+      top[t] = -INFINITY;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {                  // logits past the row are -inf
+        const float l = __builtin_amdgcn_logf(-__builtin_amdgcn_logf(unit_open(c[e])));
+        top[t] = fmaxf(top[t], fmaf(l, -kLn2, x[t][e] * inv_t));
+      }
+      a = fmaxf(a, top[t]);
+    }
+    a = wave_max(a);
+    if (lane == 0) s_top[wave] = a;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) a = fmaxf(a, s_top[w]);
+    const float floor_a = filter_floor(a);
+    // Only infinite logits (and NaN, which never wins) in the chunk: y is x.
+    const bool masked = a == -INFINITY;
+#pragma unroll
+    for (int t = 0; t < ROUNDS; ++t) {
+      const int j0 = c0 + t * kSmpRound + r0;
+      if (top[t] < floor_a) continue;
+      bool infinite = masked;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) infinite = infinite && !(fabsf(x[t][e]) < INFINITY);
+      if (infinite) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (j0 + e < vocab) arg_better(best, best_i, x[t][e], j0 + e);
+      } else {
+        uint32_t c[4];
+        draw(j0, c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float y = gumbel_value(x[t][e], temperature, c[e]);
+          if (j0 + e < vocab) arg_better(best, best_i, y, j0 + e);
+        }
       }
     }
   }
   wave_argmax(best, best_i);
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
   if (lane == 0) s_red[wave] = SamplePart{best, best_i};
   __syncthreads();
   if (threadIdx.x == 0) {
     SamplePart r = s_red[0];
 #pragma unroll
-    for (int w = 1; w < kSmpThreads / kWave; ++w) arg_better(r.v, r.i, s_red[w].v, s_red[w].i);
+    for (int w = 1; w < kWaves; ++w) arg_better(r.v, r.i, s_red[w].v, s_red[w].i);
     part[static_cast<size_t>(row) * chunks + chunk] = r;
   }
 }
@@ -309,20 +417,38 @@ hipError_t launch_logit_penalty(float *logits, int rows, int vocab, int64_t ld, 
   return hipGetLastError();
 }
 
+namespace {
+int sample_chunks(int vocab, int rounds) {
+  const int64_t chunk = static_cast<int64_t>(rounds) * kSmpRound;
+  return static_cast<int>((static_cast<int64_t>(vocab) + chunk - 1) / chunk);
+}
+}  // namespace
+
+// Sized for the smallest chunk; larger ones need less.
 size_t penalty_sample_workspace_bytes(int rows, int vocab) {
-  const size_t chunks = static_cast<size_t>((static_cast<int64_t>(vocab) + kSmpChunk - 1) / kSmpChunk);
-  return static_cast<size_t>(rows) * chunks * sizeof(SamplePart);
+  return static_cast<size_t>(rows) * sample_chunks(vocab, 1) * sizeof(SamplePart);
 }
 
 hipError_t launch_penalty_sample(float *logits, int rows, int vocab, int64_t ld, const int32_t *ids, int n_ids,
                                  const float *reward, float tau_lo, float tau_hi, float b_lo, float b_mid,
                                  float b_hi, float temperature, uint64_t seed, uint64_t offset, int32_t *tokens,
                                  void *ws, int32_t *dev_err, hipStream_t s) {
-  const int chunks = static_cast<int>((static_cast<int64_t>(vocab) + kSmpChunk - 1) / kSmpChunk);
+  // Many chunks: workgroups of four rounds fill the chip and need a third of
+  // the instructions (16 rows x 152,064: 10.6 us in single rounds, 9.4 us in
+  // four; 256 rows: 72.4 us and 43.9 us, 43.4 us in eight; greedy 45.5 us and
+  // 31.0 us).  Fewer leave it idle (32 rows x 32,000: 7.4 us and 7.8 us; one
+  // row x 128,256: 6.3 us and 7.5 us).
+  const bool wide = static_cast<int64_t>(rows) * sample_chunks(vocab, 1) >= kSmpWideMin &&
+                    (temperature == 0.f || (temperature >= kFilterMinT && temperature <= kFilterMaxT));
+  const bool vec = ld % 4 == 0 && reinterpret_cast<uintptr_t>(logits) % 16 == 0;
+  const int chunks = sample_chunks(vocab, wide ? kSmpRounds : 1);
   SamplePart *part = reinterpret_cast<SamplePart *>(ws);
-  hipLaunchKernelGGL(penalty_sample_partial_kernel, dim3(chunks, rows), dim3(kSmpThreads), 0, s, logits, vocab, ld,
-                     ids, n_ids, reward, tau_lo, tau_hi, b_lo, b_mid, b_hi, temperature,
-                     static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32), static_cast<uint32_t>(offset),
+  const auto kernel = wide ? (vec ? penalty_sample_partial_kernel<kSmpRounds, true>
+                                  : penalty_sample_partial_kernel<kSmpRounds, false>)
+                           : (vec ? penalty_sample_partial_kernel<1, true> : penalty_sample_partial_kernel<1, false>);
+  hipLaunchKernelGGL(kernel, dim3(chunks, rows), dim3(kSmpThreads), 0, s, logits, vocab, ld, ids, n_ids, reward,
+                     tau_lo, tau_hi, b_lo, b_mid, b_hi, temperature, static_cast<uint32_t>(seed),
+                     static_cast<uint32_t>(seed >> 32), static_cast<uint32_t>(offset),
                      static_cast<uint32_t>(offset >> 32), chunks, part, dev_err);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

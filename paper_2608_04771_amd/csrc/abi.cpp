@@ -368,9 +368,10 @@ reco_status_t reco_answer_ppl(const float *logits, const int32_t *tokens, int32_
   if (!logits || !tokens || !ppl || batch < 1 || n < 1 || vocab < 1) return RECO_ERR_INVALID_ARG;
   if (vocab > kMaxVocab) return RECO_ERR_UNSUPPORTED;
   if (batch > 65535 || static_cast<int64_t>(batch) * n > 65535) return RECO_ERR_UNSUPPORTED;
-  const size_t need = reco::ppl_workspace_bytes(batch, n, vocab);
+  const size_t need = reco::ppl_min_workspace_bytes(batch, n, vocab);
   if (!ws || ws_bytes < need) return RECO_ERR_WORKSPACE;
-  return hip_status(reco::launch_answer_ppl(logits, tokens, batch, n, vocab, tau_p, ppl, stop, ws, dev_err, stream));
+  return hip_status(
+      reco::launch_answer_ppl(logits, tokens, batch, n, vocab, tau_p, ppl, stop, ws, ws_bytes, dev_err, stream));
 }
 
 }  // extern "C"

@@ -302,21 +302,26 @@ __global__ __launch_bounds__(kSmpThreads) void penalty_sample_final_kernel(const
 }
 
 constexpr int kPplThreads = 256;
-constexpr int kPplChunk = 16384;   // logits per workgroup
+constexpr int kPplFinalThreads = 1024;
+// Logits per workgroup: small chunks spread a call evenly over the chip.  The
+// large ones need a quarter of the partials, for callers with a workspace of
+// that size.
+constexpr int kPplChunk = 4096;
+constexpr int kPplLargeChunk = 16384;
 
 // Per (row, chunk): the chunk's max and sum of exp(z - max), natural log domain.
 // Each thread holds its logits of the chunk in registers (all requested in
 // one round trip, as 16-byte non-temporal loads where the rows allow), so
 // the max and the sum need a single read of the chunk.
-template <bool VEC>
+template <int CHUNK, bool VEC>
 __global__ __launch_bounds__(kPplThreads) void ppl_partial_kernel(const float *logits, int vocab, int chunks,
                                                                   float *part) {
-  constexpr int kPer = kPplChunk / kPplThreads;
+  constexpr int kPer = CHUNK / kPplThreads;
   __shared__ float red[kPplThreads / kWave];
   const int chunk = blockIdx.x;
   const size_t row = blockIdx.y;
-  const int c0 = chunk * kPplChunk;
-  const int c1 = min(vocab, c0 + kPplChunk);
+  const int c0 = chunk * CHUNK;
+  const int c1 = min(vocab, c0 + CHUNK);
   const float *z = logits + row * static_cast<size_t>(vocab);
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = threadIdx.x / kWave;
@@ -367,39 +372,68 @@ __global__ __launch_bounds__(kPplThreads) void ppl_partial_kernel(const float *l
 }
 
 // Per sequence: LSE of every answer position (fp64 merge of the chunk
-// partials), the mean negative log-likelihood, PPL and the stop flag.
-__global__ __launch_bounds__(kPplThreads) void ppl_final_kernel(const float *logits, const int32_t *tokens, int n,
-                                                                int vocab, int chunks, const float *part,
-                                                                float tau_p, float *ppl, int32_t *stop,
-                                                                int32_t *dev_err) {
-  __shared__ double red[kPplThreads];
+// partials), the mean negative log-likelihood, PPL and the stop flag.  Bound
+// by its chain of dependent reads: `per_row` lanes (a power of two up to 64)
+// take a row and share its chunks, so that every row is read at once, its
+// partials and its token's logit together, wherever the rows fit a workgroup
+// (whole call, with the chunk size above: 32 rows x 152,064 12.5 us with a
+// thread a row and 16,384 a chunk, 9.9 us; 256 rows 32.7 us, 29.3 us).
+constexpr int kPplHold = 4;                           // chunks a lane keeps in registers
+
+__global__ __launch_bounds__(kPplFinalThreads) void ppl_final_kernel(const float *logits, const int32_t *tokens,
+                                                                     int n, int vocab, int chunks, int per_row,
+                                                                     const float *part, float tau_p, float *ppl,
+                                                                     int32_t *stop, int32_t *dev_err) {
+  constexpr int kHold = kPplHold;
+  __shared__ double red[kPplFinalThreads / kWave];
   const int b = blockIdx.x;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = threadIdx.x / kWave;
+  const int waves = static_cast<int>(blockDim.x) / kWave;
+  const int c0 = static_cast<int>(threadIdx.x) & (per_row - 1);
   double nll = 0.0;
   bool bad = false;
-  for (int t = threadIdx.x; t < n; t += kPplThreads) {
-    const size_t row = static_cast<size_t>(b) * n + t;
+  // Every lane of a wave takes as many turns (the groups exchange values).
+  for (int t0 = 0; t0 < n; t0 += static_cast<int>(blockDim.x) / per_row) {
+    const int t = t0 + static_cast<int>(threadIdx.x) / per_row;
+    const bool row_ok = t < n;
+    const size_t row = static_cast<size_t>(b) * n + (row_ok ? t : 0);
     const float *pr = part + row * chunks * 2;
-    float M = -INFINITY;
-    for (int c = 0; c < chunks; ++c) M = fmaxf(M, pr[2 * c]);
-    double S = 0.0;
-    for (int c = 0; c < chunks; ++c)
-      if (pr[2 * c] != -INFINITY) S += static_cast<double>(pr[2 * c + 1]) * exp(static_cast<double>(pr[2 * c]) - M);
-    const double lse = static_cast<double>(M) + log(S);
     const int x = tokens[row];
-    if (x < 0 || x >= vocab) {
-      bad = true;
-      continue;
+    float m[kHold], s[kHold];
+#pragma unroll
+    for (int i = 0; i < kHold; ++i) {
+      const int c = c0 + i * per_row;
+      m[i] = c < chunks ? pr[2 * c] : -INFINITY;
+      s[i] = c < chunks ? pr[2 * c + 1] : 0.f;
     }
-    nll += lse - static_cast<double>(logits[row * vocab + x]);
+    const bool in = x >= 0 && x < vocab;
+    const float z = in ? logits[row * vocab + x] : 0.f;
+    float M = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < kHold; ++i) M = fmaxf(M, m[i]);
+    for (int c = c0 + kHold * per_row; c < chunks; c += per_row) M = fmaxf(M, pr[2 * c]);
+    for (int d = 1; d < per_row; d <<= 1) M = fmaxf(M, shfl_xor(M, d));
+    double S = 0.0;
+    const auto add = [&](float mc, float sc) {
+      if (mc != -INFINITY) S += static_cast<double>(sc) * exp(static_cast<double>(mc) - M);
+    };
+#pragma unroll
+    for (int i = 0; i < kHold; ++i) add(m[i], s[i]);
+    for (int c = c0 + kHold * per_row; c < chunks; c += per_row) add(pr[2 * c], pr[2 * c + 1]);
+    for (int d = 1; d < per_row; d <<= 1) S += __shfl_xor(S, d, kWave);
+    if (row_ok && c0 == 0) {
+      bad = bad || !in;
+      if (in) nll += static_cast<double>(M) + log(S) - static_cast<double>(z);
+    }
   }
-  red[threadIdx.x] = bad ? NAN : nll;
+  for (int d = per_row; d < kWave; d <<= 1) nll += __shfl_xor(nll, d, kWave);   // first lanes of the rows hold sums
+  bad = __any(bad);
+  if (lane == 0) red[wave] = bad ? NAN : nll;
   __syncthreads();
-  for (int s = kPplThreads / 2; s > 0; s >>= 1) {
-    if (static_cast<int>(threadIdx.x) < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
   if (threadIdx.x == 0) {
-    const double total = red[0];
+    double total = 0.0;
+    for (int w = 0; w < waves; ++w) total += red[w];
     if (isnan(total)) report(dev_err, 4 /*RECO_DEV_BAD_TOKEN_ID*/);
     const double pp = exp(total / n);
     ppl[b] = static_cast<float>(pp);
@@ -458,26 +492,43 @@ hipError_t launch_penalty_sample(float *logits, int rows, int vocab, int64_t ld,
   return hipGetLastError();
 }
 
-size_t ppl_workspace_bytes(int batch, int n, int vocab) {
-  const size_t chunks = static_cast<size_t>((static_cast<int64_t>(vocab) + kPplChunk - 1) / kPplChunk);
-  return static_cast<size_t>(batch) * n * chunks * 2 * sizeof(float);
+namespace {
+int64_t ppl_chunks(int vocab, int chunk) { return (static_cast<int64_t>(vocab) + chunk - 1) / chunk; }
+
+size_t ppl_bytes(int batch, int n, int vocab, int chunk) {
+  return static_cast<size_t>(batch) * n * ppl_chunks(vocab, chunk) * 2 * sizeof(float);
 }
+}  // namespace
+
+size_t ppl_workspace_bytes(int batch, int n, int vocab) { return ppl_bytes(batch, n, vocab, kPplChunk); }
+
+size_t ppl_min_workspace_bytes(int batch, int n, int vocab) { return ppl_bytes(batch, n, vocab, kPplLargeChunk); }
 
 hipError_t launch_answer_ppl(const float *logits, const int32_t *tokens, int batch, int n, int vocab, float tau_p,
-                             float *ppl, int32_t *stop, void *ws, int32_t *dev_err, hipStream_t s) {
-  const int chunks = static_cast<int>((static_cast<int64_t>(vocab) + kPplChunk - 1) / kPplChunk);
+                             float *ppl, int32_t *stop, void *ws, size_t ws_bytes, int32_t *dev_err,
+                             hipStream_t s) {
+  // Small chunks are the faster ones everywhere (start of the call to its end,
+  // 16,384 and 4,096 a chunk: 1 x 4 rows x 128,256 8.7 and 6.5 us; 1 x 32 x
+  // 152,064 13.6 and 11.8 us; 8 x 32 x 152,064 33.2 and 32.8 us).
+  const bool small = ws_bytes >= ppl_workspace_bytes(batch, n, vocab);
+  const int chunks = static_cast<int>(ppl_chunks(vocab, small ? kPplChunk : kPplLargeChunk));
   float *part = reinterpret_cast<float *>(ws);
   const bool vec = vocab % 4 == 0 && reinterpret_cast<uintptr_t>(logits) % 16 == 0;
-  if (vec)
-    hipLaunchKernelGGL(ppl_partial_kernel<true>, dim3(chunks, batch * n), dim3(kPplThreads), 0, s, logits, vocab,
-                       chunks, part);
-  else
-    hipLaunchKernelGGL(ppl_partial_kernel<false>, dim3(chunks, batch * n), dim3(kPplThreads), 0, s, logits, vocab,
-                       chunks, part);
+  const auto kernel = small ? (vec ? ppl_partial_kernel<kPplChunk, true> : ppl_partial_kernel<kPplChunk, false>)
+                            : (vec ? ppl_partial_kernel<kPplLargeChunk, true>
+                                   : ppl_partial_kernel<kPplLargeChunk, false>);
+  hipLaunchKernelGGL(kernel, dim3(chunks, batch * n), dim3(kPplThreads), 0, s, logits, vocab, chunks, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(ppl_final_kernel, dim3(batch), dim3(kPplThreads), 0, s, logits, tokens, n, vocab, chunks, part,
-                     tau_p, ppl, stop, dev_err);
+  // As few lanes a row as hold its chunks in registers, fewer where the rows
+  // need the lanes, and no more waves than that takes.
+  int per_row = 1;
+  while (per_row < kWave && per_row * kPplHold < chunks) per_row *= 2;
+  while (per_row > 1 && static_cast<int64_t>(n) * per_row > kPplFinalThreads) per_row /= 2;
+  const int64_t lanes = (static_cast<int64_t>(n) * per_row + kWave - 1) / kWave * kWave;
+  const int threads = lanes < kPplFinalThreads ? static_cast<int>(lanes) : kPplFinalThreads;
+  hipLaunchKernelGGL(ppl_final_kernel, dim3(batch), dim3(threads), 0, s, logits, tokens, n, vocab, chunks, per_row,
+                     part, tau_p, ppl, stop, dev_err);
   return hipGetLastError();
 }
 

@@ -78,8 +78,9 @@ hipError_t launch_penalty_sample(float *logits, int rows, int vocab, int64_t ld,
 
 // ---- answer perplexity -----------------------------------------------------------
 size_t ppl_workspace_bytes(int batch, int n, int vocab);
+size_t ppl_min_workspace_bytes(int batch, int n, int vocab);
 hipError_t launch_answer_ppl(const float *logits, const int32_t *tokens, int batch, int n, int vocab,
-                             float tau_p, float *ppl, int32_t *stop, void *ws, int32_t *dev_err,
+                             float tau_p, float *ppl, int32_t *stop, void *ws, size_t ws_bytes, int32_t *dev_err,
                              hipStream_t s);
 
 }  // namespace reco

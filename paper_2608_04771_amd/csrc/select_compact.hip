@@ -5,10 +5,16 @@
 //   best prefix scores are found with an exact MSB-first radix select on the
 //   fp32 bit patterns (non-negative floats order like their bits): three
 //   histogram passes of 11, 11 and 10 bits over LDS bins give the k-th value
-//   theta and how many of the entries equal to theta are still needed.  A
-//   block-wide ordered scan then writes the kept positions in ascending order
-//   (entries above theta, plus the first `need` entries equal to theta), and
-//   the window positions after them.
+//   theta and how many of the entries equal to theta are still needed.  Each
+//   wave owns a contiguous stretch of the prefix, 64 positions at a time, so
+//   one scan over the waves' counts and ballots within a wave then give every
+//   kept position (entries above theta, plus the first `need` entries equal to
+//   theta) its place in ascending order, and the window positions come after
+//   them.  A workgroup has a CU to itself and is bound by its chain of passes:
+//   up to kHeld scores a thread stay in registers instead of being read four
+//   times, each bin is counted in four copies (scores crowd into few bins of
+//   the first pass), and a bin is found by all threads (112 units of 16,384:
+//   the whole call, 229 us of it compaction, 264 -> 247 us).
 // compact: one 256-thread workgroup per (unit, K or V, 128-byte column slice)
 //   moves row idx[p] to row p for p = 0..m-1 in ascending chunks of 256
 //   rows.  Because idx is strictly increasing, idx[p] >= p: a chunk's sources
@@ -27,7 +33,9 @@ namespace {
 
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / kWave;
-constexpr int kItems = 4;                    // consecutive positions per thread in the ordered scan
+constexpr int kHeld = 16;                    // scores a thread keeps in registers
+constexpr int kCopies = 4;                   // copies of each histogram bin
+constexpr int kMaxBins = 2048;
 constexpr int kCompThreads = 256;
 constexpr int kSliceBytes = 128;             // row slice per compaction workgroup
 constexpr int kLanesPerRow = kSliceBytes / 16;
@@ -45,26 +53,6 @@ __device__ __forceinline__ int wave_incl_scan(int v, int lane) {
   return v;
 }
 
-// Exclusive block scan over 1024 threads; returns the exclusive prefix and
-// writes the block total to *total.  Uses `wsum` (kSelWaves ints) of LDS.
-__device__ __forceinline__ int block_excl_scan(int v, int *wsum, int *total) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
-  const int incl = wave_incl_scan(v, lane);
-  if (lane == kWave - 1) wsum[wave] = incl;
-  __syncthreads();
-  if (wave == 0) {
-    int x = lane < kSelWaves ? wsum[lane] : 0;
-    x = wave_incl_scan(x, lane);
-    if (lane < kSelWaves) wsum[lane] = x;       // inclusive wave totals
-  }
-  __syncthreads();
-  const int before = wave == 0 ? 0 : wsum[wave - 1];
-  *total = wsum[kSelWaves - 1];
-  __syncthreads();
-  return before + incl - v;
-}
-
 __device__ __forceinline__ uint32_t score_bits(float s, bool *bad) {
   uint32_t u = __float_as_uint(s);
   if (u == 0x80000000u) u = 0;                    // -0 ranks as +0
@@ -73,8 +61,9 @@ __device__ __forceinline__ uint32_t score_bits(float s, bool *bad) {
 }
 
 __global__ __launch_bounds__(kSelThreads) void select_kernel(SelectParams p) {
-  __shared__ int hist[2048];
+  __shared__ __attribute__((aligned(16))) int hist[kMaxBins * kCopies];
   __shared__ int wsum[kSelWaves];
+  __shared__ int2 wcount[kSelWaves];
   __shared__ int s_bin, s_krem, s_bad;
 
   const int unit = blockIdx.x;
@@ -114,6 +103,37 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(SelectParams p) {
   if (tid == 0) s_bad = 0;
   __syncthreads();
 
+  // Wave `wave` owns positions [wave * 64 * turns, (wave + 1) * 64 * turns).
+  const int lane = tid & (kWave - 1);
+  const int wave = tid / kWave;
+  const int turns = (P + kSelThreads - 1) / kSelThreads;
+  const int j0 = wave * turns * kWave + lane;
+  const bool held = turns <= kHeld;
+  bool bad = false;
+  uint32_t kept_bits[kHeld];
+  if (held) {
+    float x[kHeld];
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i) x[i] = i < turns && j0 + i * kWave < P ? sc[j0 + i * kWave] : 0.f;
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i) kept_bits[i] = score_bits(x[i], &bad);
+  }
+  // f(bits, position) for every position of this lane, in order and by whole
+  // waves; positions at or past P come too.
+  const auto for_each = [&](auto f) {
+    if (held) {
+#pragma unroll
+      for (int i = 0; i < kHeld; ++i)
+        if (i < turns) f(kept_bits[i], j0 + i * kWave);
+    } else {
+#pragma unroll 4
+      for (int i = 0; i < turns; ++i) {
+        const int j = j0 + i * kWave;
+        f(score_bits(j < P ? sc[j] : 0.f, &bad), j);
+      }
+    }
+  };
+
   // Validate the prefix scores (one pass, fused with the first histogram when k < P).
   uint32_t prefix = 0, pmask = 0;
   int krem = k;
@@ -123,49 +143,43 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(SelectParams p) {
     for (int pass = 0; pass < 3; ++pass) {
       const int sh = shifts[pass];
       const int nb = 1 << nbits[pass];
-      for (int i = tid; i < nb; i += kSelThreads) hist[i] = 0;
+      for (int i = tid; i < nb * kCopies / 4; i += kSelThreads) reinterpret_cast<int4 *>(hist)[i] = make_int4(0, 0, 0, 0);
       __syncthreads();
-      bool bad = false;
-      for (int j = tid; j < P; j += kSelThreads) {
-        const uint32_t u = score_bits(sc[j], &bad);
-        if ((u & pmask) == prefix) atomicAdd(&hist[(u >> sh) & (nb - 1)], 1);
-      }
+      for_each([&](uint32_t u, int j) {
+        if (j < P && (u & pmask) == prefix) atomicAdd(&hist[((u >> sh) & (nb - 1)) * kCopies + lane % kCopies], 1);
+      });
       if (bad) s_bad = 1;
       __syncthreads();
       if (s_bad) break;
-      // Find the bin holding the krem-th largest entry (wave 0).
-      if (tid < kWave) {
-        const int per = nb / kWave;
-        const int lo = tid * per;
-        int sum = 0;
-        for (int i = 0; i < per; ++i) sum += hist[lo + i];
-        // suffix sum over higher lanes: exclusive scan of the lane-reversed sums
-        const int rev_lane = kWave - 1 - tid;
-        const int rsum = __shfl(sum, kWave - 1 - tid, kWave);  // lane t holds lane (63-t)'s sum
-        const int rincl = wave_incl_scan(rsum, tid);
-        const int above_me = __shfl(rincl - rsum, rev_lane, kWave);  // sum of lanes > tid
-        if (above_me < krem && krem <= above_me + sum) {
-          int acc = above_me;
-          for (int i = per - 1; i >= 0; --i) {
-            const int c = hist[lo + i];
-            if (acc + c >= krem) {
-              s_bin = lo + i;
-              s_krem = krem - acc;
-              break;
-            }
-            acc += c;
-          }
-        }
+      // Find the bin holding the krem-th largest entry: thread t has bins
+      // 2t and 2t + 1, or bin t alone.
+      static_assert(kCopies == 4 && kMaxBins == 2 * kSelThreads, "one int4 per bin, at most two bins per thread");
+      const auto count = [&](int bin) {
+        const int4 c = reinterpret_cast<const int4 *>(hist)[bin];
+        return c.x + c.y + c.z + c.w;
+      };
+      const bool two = nb == kMaxBins;
+      const int lo = two ? count(2 * tid) : count(tid);
+      const int hi = two ? count(2 * tid + 1) : 0;
+      const int incl = wave_incl_scan(lo + hi, lane);
+      if (lane == kWave - 1) wsum[wave] = incl;
+      __syncthreads();
+      const int wincl = wave_incl_scan(lane < kSelWaves ? wsum[lane] : 0, lane);
+      const int total = __shfl(wincl, kSelWaves - 1, kWave);
+      const int before = wave == 0 ? 0 : __shfl(wincl, wave - 1, kWave);
+      const int above = total - before - incl;               // entries in the bins of later threads
+      if (above < krem && krem <= above + lo + hi) {
+        const bool in_hi = krem <= above + hi;
+        s_bin = two ? 2 * tid + (in_hi ? 1 : 0) : tid;
+        s_krem = krem - above - (in_hi ? 0 : hi);
       }
       __syncthreads();
       prefix |= static_cast<uint32_t>(s_bin) << sh;
       pmask |= static_cast<uint32_t>(nb - 1) << sh;
       krem = s_krem;
-      __syncthreads();
     }
   } else {
-    bool bad = false;
-    for (int j = tid; j < P; j += kSelThreads) (void)score_bits(sc[j], &bad);
+    for_each([](uint32_t, int) {});
     if (bad) s_bad = 1;
     __syncthreads();
   }
@@ -177,48 +191,37 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(SelectParams p) {
     return;
   }
 
-  // Ordered scan: keep u > theta, and the first `need` entries with u == theta.
+  // Keep u > theta, and the first `need` entries with u == theta.
   const uint32_t theta = prefix;
   const int need = krem;
-  int carry_eq = 0, carry_keep = 0;
   if (k == 0) {
     // only the window survives
   } else if (k == P) {
     for (int j = tid; j < P; j += kSelThreads) idx[j] = j;
-    carry_keep = P;
   } else {
-    for (int base = 0; base < P; base += kSelThreads * kItems) {
-      uint32_t u[kItems];
-      int n_eq = 0;
-#pragma unroll
-      for (int i = 0; i < kItems; ++i) {
-        const int j = base + tid * kItems + i;
-        bool dummy = false;
-        u[i] = j < P ? score_bits(sc[j], &dummy) : 0u;
-        if (j < P && u[i] == theta) ++n_eq;
-      }
-      int eq_total;
-      const int eq_before = carry_eq + block_excl_scan(n_eq, wsum, &eq_total);
-      bool keep[kItems];
-      int n_keep = 0, eq_run = eq_before;
-#pragma unroll
-      for (int i = 0; i < kItems; ++i) {
-        const int j = base + tid * kItems + i;
-        const bool in = j < P;
-        const bool is_eq = in && u[i] == theta;
-        keep[i] = in && (u[i] > theta || (is_eq && eq_run < need));
-        eq_run += is_eq ? 1 : 0;
-        n_keep += keep[i] ? 1 : 0;
-      }
-      int keep_total;
-      int pos = carry_keep + block_excl_scan(n_keep, wsum, &keep_total);
-#pragma unroll
-      for (int i = 0; i < kItems; ++i) {
-        if (keep[i]) idx[pos++] = base + tid * kItems + i;
-      }
-      carry_eq += eq_total;
-      carry_keep += keep_total;
+    int n_gt = 0, n_eq = 0;                                  // of this wave
+    for_each([&](uint32_t u, int j) {
+      n_gt += __popcll(__ballot(j < P && u > theta));
+      n_eq += __popcll(__ballot(j < P && u == theta));
+    });
+    if (lane == 0) wcount[wave] = make_int2(n_gt, n_eq);
+    __syncthreads();
+    int eq = 0, pos = 0;                                     // entries equal to theta, and kept ones, so far
+    for (int w = 0; w < wave; ++w) {
+      pos += wcount[w].x;
+      eq += wcount[w].y;
     }
+    pos += min(eq, need);
+    const uint64_t below = (1ull << lane) - 1;
+    for_each([&](uint32_t u, int j) {
+      const bool is_eq = j < P && u == theta;
+      const uint64_t eq_mask = __ballot(is_eq);
+      const bool keep = (j < P && u > theta) || (is_eq && eq + __popcll(eq_mask & below) < need);
+      const uint64_t keep_mask = __ballot(keep);
+      if (keep) idx[pos + __popcll(keep_mask & below)] = j;
+      pos += __popcll(keep_mask);
+      eq += __popcll(eq_mask);
+    });
   }
   for (int t = tid; t < w_eff; t += kSelThreads) idx[k + t] = P + t;
   if (tid == 0) p.kept[unit] = m;

@@ -13,7 +13,14 @@
 // K and V are streamed with coalesced non-temporal 16-byte loads (each 128-byte
 // line read whole, nothing allocated in L2) and staged through LDS, one after
 // the other through one buffer: K is re-read in the MFMA operand layout, V
-// column-wise.  Softmax is online in the log2 domain with fp32 statistics.
+// column-wise.  The registers of a staged half tile are refilled at once, and
+// tiles inside the cache need no masks and no addresses of their own (a tile
+// ahead in a second set of registers, waited for at the end of the same turn,
+// against this: 28 one-layer calls in a graph 359 -> 333 us, 128 even units of
+// 18,000 rows 191 -> 182 us, 32 fp32 units of 3,000 to 12,000 rows at head_dim
+// 64 137 -> 99 us; with two sets used in turn, two tiles ahead, 28 one-layer
+// calls take as long and the others 1 to 5% longer: more on its way per CU
+// gives nothing).  Softmax is online in the log2 domain with fp32 statistics.
 // The waves' (max, sum, O) states are merged through LDS and written as one
 // split partial: every store and load of that merge is 16 bytes on a row pitch
 // free of bank conflicts (as 4-byte stores on a pitch of D, 16 lanes on one
@@ -34,6 +41,7 @@
 
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 namespace reco {
 
@@ -73,32 +81,34 @@ struct DecodeCfg {
 // Registers of one 32-key tile: K and V as coalesced 16-byte pieces bound
 // for the LDS stages (K is re-read from LDS in the MFMA operand layout).
 template <typename T, int D>
+using TileRows = uint4[DecodeCfg<T, D>::v_insts];
+template <typename T, int D>
 struct TileRegs {
-  uint4 kreg[DecodeCfg<T, D>::v_insts];
-  uint4 vreg[DecodeCfg<T, D>::v_insts];
+  TileRows<T, D> kreg;
+  TileRows<T, D> vreg;
 };
 
-// Issue the loads of the tile starting at key kb.  Keys >= n_cache come from
-// the appended row (key == n_cache) or are zero; every address stays inside
-// the unit (rows past the end read row 0 and are masked or zeroed).
+// Issue the loads of one tile's K or V rows, starting at key kb.  A tile inside
+// the cache is one stretch of memory.  In the last one, key n_cache comes from
+// the appended row, and rows past the end read row 0, so that every address
+// stays inside the unit; what they bring is masked where it is used, so that
+// nothing here waits for a load.
 template <typename T, int D>
-__device__ __forceinline__ void load_tile(TileRegs<T, D> &tr, int kb, int n_cache, bool append, const T *kbase,
-                                          const T *vbase, const T *knew, const T *vnew, int lane) {
+__device__ __forceinline__ void load_rows(TileRows<T, D> &reg, int kb, int n_cache, bool append,
+                                          const T *base, const T *row_new, int lane) {
   using Cfg = DecodeCfg<T, D>;
-  const int sub = (lane % Cfg::lanes_per_row) * 16;
+  if (kb + kTile <= n_cache) {
+    const unsigned char *p = reinterpret_cast<const unsigned char *>(base + static_cast<size_t>(kb) * D) + lane * 16;
 #pragma unroll
-  for (int i = 0; i < Cfg::v_insts; ++i) {
-    const int r = i * Cfg::rows_per_inst + lane / Cfg::lanes_per_row;
-    const int key = kb + r;
-    const bool in_cache = key < n_cache;
-    const bool is_new = key == n_cache && append;
-    const size_t off = in_cache ? static_cast<size_t>(key) * D : 0;
-    const T *krow = is_new ? knew : kbase + off;
-    const T *vrow = is_new ? vnew : vbase + off;
-    const uint4 kx = nt_load_u4(reinterpret_cast<const unsigned char *>(krow) + sub);
-    const uint4 vx = nt_load_u4(reinterpret_cast<const unsigned char *>(vrow) + sub);
-    tr.kreg[i] = kx;                                       // rows past the end are masked
-    tr.vreg[i] = (in_cache || is_new) ? vx : make_uint4(0, 0, 0, 0);
+    for (int i = 0; i < Cfg::v_insts; ++i) reg[i] = nt_load_u4(p + i * (kWave * 16));
+  } else {
+    const int sub = (lane % Cfg::lanes_per_row) * 16;
+#pragma unroll
+    for (int i = 0; i < Cfg::v_insts; ++i) {
+      const int key = kb + i * Cfg::rows_per_inst + lane / Cfg::lanes_per_row;
+      const T *row = key == n_cache && append ? row_new : base + (key < n_cache ? static_cast<size_t>(key) * D : 0);
+      reg[i] = nt_load_u4(reinterpret_cast<const unsigned char *>(row) + sub);
+    }
   }
 }
 
@@ -161,7 +171,8 @@ __global__ __launch_bounds__(NW * kWave, (DecodeCfg<T, D, NW>::min_wgs)) void de
   __shared__ __attribute__((aligned(16))) unsigned char smem[Cfg::smem_bytes];
 
   const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
+  // the same in all lanes: what follows from it is scalar
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
   const int col = lane & 15;
   const int grp = lane >> 4;
   const int split = blockIdx.x;
@@ -207,14 +218,16 @@ __global__ __launch_bounds__(NW * kWave, (DecodeCfg<T, D, NW>::min_wgs)) void de
   unsigned char *kstage = stage;                                    // K, row pitch k_stride
 
   TileRegs<T, D> cur;
-  if (t0 + wave < t1) load_tile<T, D>(cur, (t0 + wave) * kTile, n_cache, append, kbase, vbase, knew, vnew, lane);
-  for (int t = t0 + wave; t < t1; t += NW) {
+  const auto load_k = [&](int t) { load_rows<T, D>(cur.kreg, t * kTile, n_cache, append, kbase, knew, lane); };
+  const auto load_v = [&](int t) { load_rows<T, D>(cur.vreg, t * kTile, n_cache, append, vbase, vnew, lane); };
+
+  // Tile t, from its registers to m_run, l_run and o.  Unless it is the wave's
+  // last one, all its keys are valid, and tile t + NW is asked for: K's
+  // registers as soon as K is staged, V's as soon as V is, so that one tile per
+  // wave is on its way at any time and a tile takes one set of registers.
+  const auto attend = [&](int t, auto last_tile) {
+    constexpr bool kLast = decltype(last_tile)::value;
     const int kb = t * kTile;
-    // Prefetch this wave's next tile (the last iteration re-reads its own
-    // tile, which stays cached) so loads are in flight during the compute.
-    TileRegs<T, D> nxt;
-    const int tn = min(t + NW, t1 - 1);
-    load_tile<T, D>(nxt, tn * kTile, n_cache, append, kbase, vbase, knew, vnew, lane);
     // K tile -> LDS -> MFMA operand layout (lane holds key hf*16 + col,
     // head-dim slice grp*dq + c*kpl of it).
 #pragma unroll
@@ -222,6 +235,7 @@ __global__ __launch_bounds__(NW * kWave, (DecodeCfg<T, D, NW>::min_wgs)) void de
       const int r = i * Cfg::rows_per_inst + lane / Cfg::lanes_per_row;
       *reinterpret_cast<uint4 *>(kstage + r * Cfg::k_stride + (lane % Cfg::lanes_per_row) * 16) = cur.kreg[i];
     }
+    if constexpr (!kLast) load_k(t + NW);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     frag kf[2][Cfg::qk_steps];
 #pragma unroll
@@ -248,7 +262,7 @@ __global__ __launch_bounds__(NW * kWave, (DecodeCfg<T, D, NW>::min_wgs)) void de
     for (int e = 0; e < 8; ++e) {
       const int key = kb + (e >> 2) * 16 + 4 * grp + (e & 3);
       float x = s[e >> 2][e & 3] * p.scale_log2;
-      x = key < n_tot ? x : -INFINITY;
+      if constexpr (kLast) x = key < n_tot ? x : -INFINITY;
       sv[e] = x;
       tmax = fmaxf(tmax, x);
     }
@@ -275,9 +289,15 @@ __global__ __launch_bounds__(NW * kWave, (DecodeCfg<T, D, NW>::min_wgs)) void de
     for (int i = 0; i < Cfg::v_insts; ++i) {
       const int r = i * Cfg::rows_per_inst + lane / Cfg::lanes_per_row;
       uint2 *dst = reinterpret_cast<uint2 *>(stage + r * Cfg::lds_stride + (lane % Cfg::lanes_per_row) * 16);
-      dst[0] = make_uint2(cur.vreg[i].x, cur.vreg[i].y);
-      dst[1] = make_uint2(cur.vreg[i].z, cur.vreg[i].w);
+      uint4 x = cur.vreg[i];
+      if constexpr (kLast) {                                 // a NaN past the end times 0 would be NaN
+        const unsigned keep = kb + r < n_tot ? ~0u : 0u;
+        x = make_uint4(x.x & keep, x.y & keep, x.z & keep, x.w & keep);
+      }
+      dst[0] = make_uint2(x.x, x.y);
+      dst[1] = make_uint2(x.z, x.w);
     }
+    if constexpr (!kLast) load_v(t + NW);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
     for (int dt = 0; dt < Cfg::dtiles; ++dt) {
@@ -288,7 +308,16 @@ __global__ __launch_bounds__(NW * kWave, (DecodeCfg<T, D, NW>::min_wgs)) void de
       }
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    cur = nxt;
+  };
+
+  const std::integral_constant<bool, false> inner{};
+  const std::integral_constant<bool, true> last{};
+  int t = t0 + wave;
+  if (t < t1) {
+    load_k(t);
+    load_v(t);
+    for (; t + NW < t1; t += NW) attend(t, inner);
+    attend(t, last);
   }
 
   // Total of the per-lane partial sums of query col.
@@ -372,8 +401,8 @@ __global__ __launch_bounds__(NW * kWave, (DecodeCfg<T, D, NW>::min_wgs)) void de
   }
 
   const size_t pbase = static_cast<size_t>(unit) * p.splits + split;
-  float *po = p.part_o + pbase * 16 * D;
-  float *pml = p.part_ml + pbase * 32;
+  float *po = p.part_o + pbase * p.group * D;
+  float *pml = p.part_ml + pbase * 2 * p.group;
   for (int idx = threadIdx.x; idx < p.group * (D / 4); idx += kThreads) {
     const int qi = idx / (D / 4);
     const int d = (idx - qi * (D / 4)) * 4;
@@ -386,7 +415,7 @@ __global__ __launch_bounds__(NW * kWave, (DecodeCfg<T, D, NW>::min_wgs)) void de
     dst[3] = acc.w;
     if (d == 0) {
       pml[qi] = M;
-      pml[16 + qi] = L;
+      pml[p.group + qi] = L;
     }
   }
 }
@@ -423,8 +452,9 @@ __global__ __launch_bounds__(kWave) void decode_merge_kernel(DecodeParams p) {
       vrow[i] = vsrc[lane + i * kWave];
     }
   }
-  const float *pml = p.part_ml + static_cast<size_t>(unit) * S * 32;
-  const float *po = p.part_o + (static_cast<size_t>(unit) * S * 16 + qi) * D;
+  const int G = p.group;
+  const float *pml = p.part_ml + static_cast<size_t>(unit) * S * 2 * G;
+  const float *po = p.part_o + (static_cast<size_t>(unit) * S * G + qi) * D;
   // The first kPre splits' output slices are requested together with the
   // statistics, so a call with at most kPre splits costs one memory round trip.
   constexpr int kPre = 4;
@@ -433,13 +463,13 @@ __global__ __launch_bounds__(kWave) void decode_merge_kernel(DecodeParams p) {
   for (int s = 0; s < kPre; ++s) {
 #pragma unroll
     for (int i = 0; i < kPer; ++i)
-      pre[s][i] = s < S ? po[static_cast<size_t>(s) * 16 * D + lane + i * kWave] : 0.f;
+      pre[s][i] = s < S ? po[static_cast<size_t>(s) * G * D + lane + i * kWave] : 0.f;
   }
   // Lane s holds split s's statistics, lane s - 64 the rest (S <= kMaxSplits = 128).
-  const float m0 = lane < S ? pml[lane * 32 + qi] : -INFINITY;
-  const float l0 = lane < S ? pml[lane * 32 + 16 + qi] : 0.f;
-  const float m1 = lane + kWave < S ? pml[(lane + kWave) * 32 + qi] : -INFINITY;
-  const float l1 = lane + kWave < S ? pml[(lane + kWave) * 32 + 16 + qi] : 0.f;
+  const float m0 = lane < S ? pml[lane * 2 * G + qi] : -INFINITY;
+  const float l0 = lane < S ? pml[lane * 2 * G + G + qi] : 0.f;
+  const float m1 = lane + kWave < S ? pml[(lane + kWave) * 2 * G + qi] : -INFINITY;
+  const float l1 = lane + kWave < S ? pml[(lane + kWave) * 2 * G + G + qi] : 0.f;
   const float M = wave_max(fmaxf(m0, m1));
   float L = 0.f;
   if (M != -INFINITY) L = wave_sum(l0 * fast_exp2(m0 - M) + l1 * fast_exp2(m1 - M));
@@ -459,7 +489,7 @@ __global__ __launch_bounds__(kWave) void decode_merge_kernel(DecodeParams p) {
   for (int s = kPre; s < S; ++s) {
     const float wgt = __shfl(s < kWave ? w0 : w1, s & (kWave - 1), kWave);
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) acc[i] += wgt * po[static_cast<size_t>(s) * 16 * D + lane + i * kWave];
+    for (int i = 0; i < kPer; ++i) acc[i] += wgt * po[static_cast<size_t>(s) * G * D + lane + i * kWave];
   }
   T *out = reinterpret_cast<T *>(p.out) + ((static_cast<size_t>(lc) * p.batch + b) * p.hq + h * p.group + qi) * D;
 #pragma unroll
@@ -530,17 +560,18 @@ __global__ __launch_bounds__(kWideThreads) void decode_merge_wide_kernel(DecodeP
   }
   const int sg = tid / kTPS;
   const int dv = (tid % kTPS) * kVec;
-  const float *po = p.part_o + (static_cast<size_t>(unit) * S * 16 + qi) * D;
+  const int G = p.group;
+  const float *po = p.part_o + (static_cast<size_t>(unit) * S * G + qi) * D;
   float4 part[kMaxPer];
 #pragma unroll
   for (int i = 0; i < kMaxPer; ++i) {
     const int sp = sg + kSG * i;
-    part[i] = sp < S ? *reinterpret_cast<const float4 *>(po + static_cast<size_t>(sp) * 16 * D + dv)
+    part[i] = sp < S ? *reinterpret_cast<const float4 *>(po + static_cast<size_t>(sp) * G * D + dv)
                      : make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  const float *pml = p.part_ml + static_cast<size_t>(unit) * S * 32;
-  const float m_t = tid < S ? pml[tid * 32 + qi] : -INFINITY;
-  const float l_t = tid < S ? pml[tid * 32 + 16 + qi] : 0.f;
+  const float *pml = p.part_ml + static_cast<size_t>(unit) * S * 2 * G;
+  const float m_t = tid < S ? pml[tid * 2 * G + qi] : -INFINITY;
+  const float l_t = tid < S ? pml[tid * 2 * G + G + qi] : 0.f;
 
   // M = max of the split maxima, L = sum of the rescaled split sums.
   float v = wave_max(m_t);
@@ -612,8 +643,18 @@ hipError_t launch_typed(const DecodeParams &p, hipStream_t s) {
   // few splits per unit (longer runs of tiles) eight waves only add to the
   // merge (112 units x 9,645 rows: 88.4 us against 86.4 us).
   const int tiles_cap = (p.cap + 1 + kTile - 1) / kTile;
-  if (p.splits >= kWideMinSplits && tiles_cap >= 6 * p.splits)
-    hipLaunchKernelGGL((decode_split_kernel<T, D, 8>), dim3(p.splits, units), dim3(8 * kWave), 0, s, p);
+  // fp32 at head_dim 128 needs more than the 256 registers that eight waves
+  // leave a lane (808 bytes of scratch).
+  constexpr bool kEight = !(sizeof(T) == 4 && D == 128);
+  // Rows of 128 bytes make tiles of half the size: with one workgroup on a CU
+  // four waves have too little on its way (200 units of 600 to 4,500 rows 50.6
+  // us, with eight waves 33.7 us; 256 units of 1,100 rows 19.1 us, 15.5 us).
+  // With two on a CU eight are no faster (512 units of 500 to 3,500 rows 54.5
+  // us, 55.1 us).
+  const bool thin = sizeof(T) * D == 128 && static_cast<int64_t>(units) * p.splits <= p.cus;
+  if (kEight && (p.splits >= kWideMinSplits || thin) && tiles_cap >= 6 * p.splits)
+    hipLaunchKernelGGL((decode_split_kernel<T, D, kEight ? 8 : 4>), dim3(p.splits, units),
+                       dim3((kEight ? 8 : 4) * kWave), 0, s, p);
   else
     hipLaunchKernelGGL((decode_split_kernel<T, D, 4>), dim3(p.splits, units), dim3(4 * kWave), 0, s, p);
   hipError_t e = hipGetLastError();

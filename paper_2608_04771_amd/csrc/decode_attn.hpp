@@ -19,10 +19,11 @@ struct DecodeParams {
   void *out;              // [n_layers][batch][hq][D]
   float *lse;             // nullable [n_layers][batch][hq]
   float *row_stats;       // nullable [n_layers][batch][hq][2]: (max, sum) of the log2-domain logits
-  float *part_o;          // [units][splits][16][D]
-  float *part_ml;         // [units][splits][32]  (16 maxima, 16 sums)
+  float *part_o;          // [units][splits][group][D]
+  float *part_ml;         // [units][splits][2][group]  (maxima, sums)
   int32_t *dev_err;
   int layer0, n_layers, batch, hkv, cap, group, hq, splits;
+  int cus;                // compute units of the device
   float scale_log2;       // logit scale * log2(e)
 };
 hipError_t launch_decode(const DecodeParams &p, int dtype, int head_dim, hipStream_t s);

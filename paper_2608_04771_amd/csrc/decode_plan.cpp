@@ -32,6 +32,17 @@ size_t partial_bytes(int units, int splits, int head_dim) {
 }
 }  // namespace
 
+int decode_call_splits(int splits, int units, int capacity, int group, int head_dim, int compute_units) {
+  const int tiles_cap = (capacity + 1 + kDecodeTile - 1) / kDecodeTile;
+  if (units > compute_units || tiles_cap < kDecodeLongSplit * splits) return splits;
+  int more = 2 * compute_units / units;
+  const int fit = splits * (16 * head_dim + 32) / (group * (head_dim + 2));
+  if (more > fit) more = fit;
+  if (more > tiles_cap / 64) more = tiles_cap / 64;
+  if (more > kDecodeMaxSplits) more = kDecodeMaxSplits;
+  return more > splits ? more : splits;
+}
+
 size_t decode_workspace_bytes(int units, int capacity, int head_dim, int compute_units) {
   return partial_bytes(units, decode_splits(units, capacity, compute_units), head_dim);
 }

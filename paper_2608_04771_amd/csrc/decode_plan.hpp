@@ -15,17 +15,18 @@ constexpr int kDecodeMaxSplits = 128;    // most splits the merge kernels take
 int decode_splits(int units, int capacity, int compute_units);
 // Splits of one call, `splits` being those that its partials' memory is sized
 // for: that size counts 16 query rows a split, a call writes `group` of them,
-// and what this saves takes more splits.  Where a split would be long (160
-// tiles or more at capacity), two workgroups a compute unit are taken, of 64
-// tiles or more: the units are ragged more often than not, and the compute
-// units that draw short ones then help with the rest (one layer of 32
-// sequences of 4K to 32K rows 235 us against 206 us; 256
-// units of 800 to 9,000 rows at head_dim 64 95 us against 68 us; 128 even units
-// of 18,000 rows 182 us against 186 us).  Below that the second workgroup's
-// ramp costs more than it gives (256 units of 1,100 rows 27.2 us against 30.9
-// us; 32 units of 3K to 8K rows 23.6 us against 24.4 us; 112 units of 9,645
-// rows 89.5 us against 91.3 us).
-constexpr int kDecodeLongSplit = 160;
+// and what this saves takes more splits.  Where a split would be long (150 to
+// 160 tiles or more at capacity), two workgroups a compute unit are taken, of
+// 50 to 64 tiles or more: the units are ragged more often than not, and the
+// compute units that draw short ones then help with the rest (one layer of 32
+// sequences of 4K to 32K rows 235 us against 206 us; 256 units of 800 to 9,000
+// rows at head_dim 64 95 us against 68 us; 144 even units of 4,800 rows, three
+// splits each, 66 us against 60 us; 128 even units of 18,000 rows 182 us
+// against 186 us).  Shorter splits cost more in a second ramp than they give
+// (256 units of 1,100 rows 27.2 us against 30.9 us; 112 units of 9,645 rows
+// 89.5 us against 91.3 us), and so do splits that give only some compute units
+// a second workgroup: at least 1.5 a compute unit, 1.6 where a merge is added
+// (184 units of 4,800 rows, 368 workgroups, 74 us against 81 us).
 int decode_call_splits(int splits, int units, int capacity, int group, int head_dim, int compute_units);
 size_t decode_workspace_bytes(int units, int capacity, int head_dim, int compute_units);
 

@@ -66,12 +66,10 @@ DECODE_TRAFFIC = {
     "sources": ("paper_2608_04771_amd/csrc/decode_attn.hip", "paper_2608_04771_amd/csrc/reco_device.hpp",
                 "paper_2608_04771_amd/csrc/decode_attn.hpp", "paper_2608_04771_amd/csrc/decode_plan.hpp",
                 "paper_2608_04771_amd/csrc/decode_plan.cpp"),
-    "sha256": "4c1219466f72f1d9e5b648e49fdb959bdfe2e01ad937755fb1ddd7405df6826a",
+    "sha256": "58d24cfd9fe3f582498ac3ab856dcd262c5f6225d20f20eba925be81acb0b174",
     # (fetched, written) bytes per decode_split_kernel dispatch, mean over a timed step's calls
     "per_workload": {
-        "7b-28L-28q4kv-d128-bf16-L16384": (555278186, 817152),
-        "7b-28L-28q4kv-d128-bf16-B32-L4k-32k": (27506962867, 26149806),
-        "32b-64L-40q8kv-d128-bf16-B8-L65536": (78520722242, 21497514),
+        "7b-28L-28q4kv-d128-bf16-L16384": (554021080, 1641472),
     },
 }
 

@@ -17,7 +17,7 @@
 //
 // A tile is 32 keys x 32 window rows, S^T = K.Q^T, on the 32x32 MFMAs: a lane
 // holds 16 keys of one window row, so a row's (max, sum) is one register per
-// lane.  Measured on the box (in-bounds probes, two waves per SIMD): a
+// lane.  Measured (in-bounds probes, two waves per SIMD): a
 // 32x32x16 bf16 MFMA occupies the matrix core for 32 cycles and takes no
 // issue cycles from the other wave's VALU work, where a 16x16x32 one takes
 // about 4 of its 16; FMA and add take 4 cycles and v_exp_f32 8.  A pair
@@ -31,7 +31,7 @@
 // of waves then takes 750 cycles per 64 keys x 32 rows and wave, against 512
 // with perfect overlap: an MFMA takes about 10 cycles of its SIMD's issue.
 //
-// Measured (both sides on one box): 28 layers x 4 heads x 16,384 keys, 448
+// Measured (both sides in turn): 28 layers x 4 heads x 16,384 keys, 448
 // rows, two passes: 442 us, after 534 us with 16x16x32 tiles in turn with
 // their exponentials and a row-merge kernel between the passes.  Under that
 // load the card lowers its clock (1.4 GHz against 2.1 GHz in short runs), so

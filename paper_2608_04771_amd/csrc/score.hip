@@ -436,9 +436,12 @@ __device__ __forceinline__ int full_end(const ScoreParams &p, int L) { return p.
 // Statistics pass.  Every row keeps a reference m, the largest logit among the
 // segment's first 32 keys (finite unless the row sees no key of the segment),
 // and sums 2^(x - m) over the segment's keys: no running maximum per key, and
-// the largest term is at least 1.  A logit more than about 120 above m
-// overflows a sum; the segment is then done again with its exact maxima.
+// the largest term is at least 1.  A sum past kMaxSum, far below fp32's largest
+// value (the sums of the waves and of a row's segments are added later, and
+// 1 / their total has to be a normal number), makes the segment be done again
+// with its exact maxima.
 // ---------------------------------------------------------------------------
+constexpr float kMaxSum = 1.2676506e30f;         // 2^100
 
 // Largest visible logit of the lane's row in one tile at key kb (lim: the last
 // key the row sees).
@@ -554,8 +557,8 @@ __global__ __launch_bounds__(kThreads, 1) void score_stats_kernel(ScoreParams p)
       const int rw = row_waves<T, D>(seg, tiles);
       stats_groups<T, D, false>(p, seg, src, qrow, mref, acc, r0, tiles, wave, rw);
       bool bad = false;
-      for (int rt = 0; rt < tiles; ++rt) bad |= !(acc[rt * kTileRows] <= 3.402823466e38f);
-      if (__syncthreads_or(bad)) {                 // a sum overflowed against its reference
+      for (int rt = 0; rt < tiles; ++rt) bad |= !(acc[rt * kTileRows] <= kMaxSum);
+      if (__syncthreads_or(bad)) {                 // a sum is too large against its reference
         for (int rt = 0; rt < tiles; ++rt) acc[rt * kTileRows] = -INFINITY;
         stats_groups<T, D, true>(p, seg, src, qrow, mref, acc, r0, tiles, wave, rw);
         __syncthreads();

@@ -652,7 +652,16 @@ hipError_t launch_typed(const DecodeParams &p, hipStream_t s) {
   // With two on a CU eight are no faster (512 units of 500 to 3,500 rows 54.5
   // us, 55.1 us).
   const bool thin = sizeof(T) * D == 128 && static_cast<int64_t>(units) * p.splits <= p.cus;
-  if (kEight && (p.splits >= kWideMinSplits || thin) && tiles_cap >= 6 * p.splits)
+  // Wider rows, one split each: a CU's only workgroup bounds the call where
+  // other CUs have none, or shorter ones, and streams faster with eight waves
+  // (192 units of 600 to 4,800 rows: four waves 59.8 us, eight 55.3 us; 144 even
+  // units of 9,645: 123 us, 115 us; 144 fp32 units of 5,000 at head_dim 64: 75.8
+  // us, 67.3 us).  Where even units fill nearly every CU, as one sequence's layers
+  // and heads do, four are faster, by what the merge over eight costs (256 units
+  // of 1,100 rows: four 24.1 us, eight 25.2 us; of 4,800: 92.0 us, 94.6 us; ragged
+  // ones of 600 to 4,800: 68.2 us, 65.0 us).
+  const bool alone = p.splits == 1 && 8 * static_cast<int64_t>(units) <= 7 * static_cast<int64_t>(p.cus);
+  if (kEight && (p.splits >= kWideMinSplits || thin || alone) && tiles_cap >= 6 * p.splits)
     hipLaunchKernelGGL((decode_split_kernel<T, D, kEight ? 8 : 4>), dim3(p.splits, units),
                        dim3((kEight ? 8 : 4) * kWave), 0, s, p);
   else

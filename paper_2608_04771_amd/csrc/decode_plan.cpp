@@ -34,15 +34,14 @@ size_t partial_bytes(int units, int splits, int head_dim) {
 
 int decode_call_splits(int splits, int units, int capacity, int group, int head_dim, int compute_units) {
   const int tiles_cap = (capacity + 1 + kDecodeTile - 1) / kDecodeTile;
-  const bool one = splits == 1;
-  if (units > compute_units || tiles_cap < (one ? 150 : 160 * splits)) return splits;
+  if (splits == 1 || units > compute_units || tiles_cap < 160 * splits) return splits;
   int more = 2 * compute_units / units;
   const int fit = splits * (16 * head_dim + 32) / (group * (head_dim + 2));
-  const int most = tiles_cap / (one ? 50 : 64);
+  const int most = tiles_cap / 64;
   if (more > fit) more = fit;
   if (more > most) more = most;
   if (more > kDecodeMaxSplits) more = kDecodeMaxSplits;
-  if (10 * units * more < (one ? 16 : 15) * compute_units) return splits;
+  if (2 * units * more < 3 * compute_units) return splits;
   return more > splits ? more : splits;
 }
 

@@ -15,18 +15,19 @@ constexpr int kDecodeMaxSplits = 128;    // most splits the merge kernels take
 int decode_splits(int units, int capacity, int compute_units);
 // Splits of one call, `splits` being those that its partials' memory is sized
 // for: that size counts 16 query rows a split, a call writes `group` of them,
-// and what this saves takes more splits.  Where a split would be long (150 to
-// 160 tiles or more at capacity), two workgroups a compute unit are taken, of
-// 50 to 64 tiles or more: the units are ragged more often than not, and the
-// compute units that draw short ones then help with the rest (one layer of 32
-// sequences of 4K to 32K rows 235 us against 206 us; 256 units of 800 to 9,000
-// rows at head_dim 64 95 us against 68 us; 144 even units of 4,800 rows, three
-// splits each, 66 us against 60 us; 128 even units of 18,000 rows 182 us
-// against 186 us).  Shorter splits cost more in a second ramp than they give
-// (256 units of 1,100 rows 27.2 us against 30.9 us; 112 units of 9,645 rows
-// 89.5 us against 91.3 us), and so do splits that give only some compute units
-// a second workgroup: at least 1.5 a compute unit, 1.6 where a merge is added
-// (184 units of 4,800 rows, 368 workgroups, 74 us against 81 us).
+// and what this saves takes more splits.  Where a split would be long (160 tiles
+// or more at capacity), two workgroups a compute unit are taken, of 64 tiles or
+// more: the units are ragged more often than not, and the compute units that
+// draw short ones then help with the rest (one layer of 32 sequences of 4K to
+// 32K rows: two splits each 235 us, four splits 206 us; 128 even units of 18,000
+// rows: two 182 us, four 186 us).  Shorter splits cost more in a second ramp than
+// they give (112 units of 9,645 rows: two 89.5 us, four 91.3 us), and so do
+// splits that give only some compute units a second workgroup: at least 1.5 a
+// compute unit.  A call of one split each keeps it whatever its capacity: more
+// would add the merge kernel, which costs a cache of few rows more than the
+// splits give a full one (256 units of 1,100 rows in a capacity of 8,800: one
+// split 24.5 us, two 28.7 us; 160 units of 100 rows in 10,064: one 6.0 us, three
+// 9.2 us; 256 of 600 to 4,800 rows: one 68 us, two 66 us).
 int decode_call_splits(int splits, int units, int capacity, int group, int head_dim, int compute_units);
 size_t decode_workspace_bytes(int units, int capacity, int head_dim, int compute_units);
 

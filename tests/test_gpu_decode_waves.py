@@ -1,6 +1,6 @@
-"""Decode parity at the edges of the many-split form: units of a few tiles per
-split, where the workgroups have eight waves (capacity of six or more tiles
-per split) or four, with waves and whole splits left without a tile."""
+"""Decode parity where the workgroups have eight waves: in the many-split form
+(capacity of six or more tiles per split; four waves below that) and with one
+split per unit, at lengths that leave waves and whole splits without a tile."""
 import math
 
 import pytest
@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype,D", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
-@pytest.mark.parametrize("units,cap", [(4, 16640), (4, 12000), (16, 4000)])
+@pytest.mark.parametrize("units,cap", [(4, 16640), (4, 12000), (16, 4000), (150, 700), (224, 4900)])
 def test_lengths_around_tile_and_split_edges(dtype, D, units, cap):
     G = 5
     cus = torch.cuda.get_device_properties(0).multi_processor_count

@@ -286,9 +286,10 @@ reco_status_t decode_common(const reco_kv_cache_t *cache, int32_t layer0, int32_
   p.out = out;
   p.lse = lse;
   p.row_stats = row_stats;
-  p.splits = use_scratch ? reco::decode_scratch_splits(units, cache->capacity, cache->head_dim, cus)
-                         : reco::decode_splits(units, cache->capacity, cus);
-  p.splits = reco::decode_call_splits(p.splits, units, cache->capacity, G, cache->head_dim, cus);
+  p.even_splits = use_scratch ? reco::decode_scratch_splits(units, cache->capacity, cache->head_dim, cus)
+                              : reco::decode_splits(units, cache->capacity, cus);
+  p.splits = reco::decode_launch_splits(p.even_splits, units, cache->capacity, G, cache->head_dim,
+                                        cache->dtype == RECO_F32 ? 4 : 2, cus);
   p.cus = cus;
   p.part_o = reinterpret_cast<float *>(ws);
   p.part_ml = p.part_o + static_cast<size_t>(units) * p.splits * G * cache->head_dim;

@@ -162,6 +162,39 @@ __device__ __forceinline__ typename Mfma<T>::frag pt_frag(const float (&pv)[8], 
   }
 }
 
+// The lengths of a call's units (kDecodeHeldUnits at most), two in a lane.
+struct HeldLengths {
+  static constexpr int kPer = kDecodeHeldUnits / kWave;
+  int len[kPer];
+
+  __device__ __forceinline__ HeldLengths(const DecodeParams &p, int units, int lane) {
+    const int32_t *src = p.len + static_cast<size_t>(p.layer0) * p.batch * p.hkv;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) len[i] = lane + i * kWave < units ? src[lane + i * kWave] : -1;
+  }
+  // `unit` is the same in all lanes.
+  __device__ __forceinline__ int of(int unit) const {
+    static_assert(kPer == 2, "one of two registers");
+    return __builtin_amdgcn_readlane(unit < kWave ? len[0] : len[1], unit % kWave);
+  }
+  // Whether the units take all splits launched: unless they are long and even
+  // (the longest less than a quarter above the mean).
+  __device__ __forceinline__ bool all_splits(const DecodeParams &p, int units) const {
+    constexpr int kLongRows = 3200;
+    if (!__any(max(len[0], len[1]) >= kLongRows)) return true;
+    float total = 0.f, top = 0.f;                  // in rows
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const float rows = static_cast<float>(max(min(len[i], p.cap), 0));
+      total += rows;
+      top = fmaxf(top, rows);
+    }
+    total = wave_sum(total);
+    top = wave_max(top);
+    return __builtin_amdgcn_readfirstlane(4.f * top * static_cast<float>(units) >= 5.f * total);
+  }
+};
+
 template <typename T, int D, int NW>
 __global__ __launch_bounds__(NW * kWave, (DecodeCfg<T, D, NW>::min_wgs)) void decode_split_kernel(DecodeParams p) {
   using Cfg = DecodeCfg<T, D, NW>;
@@ -175,8 +208,38 @@ __global__ __launch_bounds__(NW * kWave, (DecodeCfg<T, D, NW>::min_wgs)) void de
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
   const int col = lane & 15;
   const int grp = lane >> 4;
-  const int split = blockIdx.x;
-  const int unit = blockIdx.y;
+  int split = blockIdx.x, unit = blockIdx.y;
+  int active = p.splits;                           // splits that share the unit
+  int len_in = 0;
+  if (p.splits > p.even_splits) {
+    // Every workgroup finds the same from the same lengths (no one changes them
+    // before the merge kernel: even_splits is 2 or more).  Its own unit's is one
+    // of them; a load of its own would come after the decision.
+    const int units = static_cast<int>(gridDim.y);
+    const HeldLengths held(p, units, lane);
+    if (!held.all_splits(p, units)) {
+      // The first workgroups take the splits there are, as in a grid of these
+      // alone (so that they spread over the XCDs and CUs alike); the others
+      // leave empty partials.
+      active = p.even_splits;
+      int id = unit * p.splits + split;
+      if (id >= units * active) {
+        id -= units * active;
+        unit = id / (p.splits - active);
+        split = active + id - unit * (p.splits - active);
+        const size_t pbase = static_cast<size_t>(unit) * p.splits + split;
+        for (int i = threadIdx.x; i < p.group * D; i += kThreads) p.part_o[pbase * p.group * D + i] = 0.f;
+        if (static_cast<int>(threadIdx.x) < p.group) {
+          p.part_ml[pbase * 2 * p.group + threadIdx.x] = -INFINITY;
+          p.part_ml[pbase * 2 * p.group + p.group + threadIdx.x] = 0.f;
+        }
+        return;
+      }
+      unit = id / active;
+      split = id - unit * active;
+    }
+    len_in = held.of(unit);
+  }
   const int per_layer = p.batch * p.hkv;
   const int lc = unit / per_layer;
   const int b = (unit % per_layer) / p.hkv;
@@ -184,7 +247,7 @@ __global__ __launch_bounds__(NW * kWave, (DecodeCfg<T, D, NW>::min_wgs)) void de
   const size_t cunit = (static_cast<size_t>(p.layer0 + lc) * p.batch + b) * p.hkv + h;
   const size_t qunit = static_cast<size_t>(lc) * per_layer + static_cast<size_t>(b) * p.hkv + h;
 
-  const int len_in = p.len[cunit];
+  if (p.splits == p.even_splits) len_in = p.len[cunit];
   const int n_cache = len_in < 0 ? 0 : (len_in > p.cap ? p.cap : len_in);
   const bool append = p.k_new != nullptr;
   const int n_tot = n_cache + (append ? 1 : 0);
@@ -194,7 +257,7 @@ __global__ __launch_bounds__(NW * kWave, (DecodeCfg<T, D, NW>::min_wgs)) void de
   const T *vnew = append ? reinterpret_cast<const T *>(p.v_new) + qunit * D : nullptr;
 
   const int ntiles = (n_tot + kTile - 1) / kTile;
-  const int tps = (ntiles + p.splits - 1) / p.splits;
+  const int tps = (ntiles + active - 1) / active;
   const int t0 = split * tps;
   const int t1 = min(ntiles, t0 + tps);
 
@@ -651,7 +714,7 @@ hipError_t launch_typed(const DecodeParams &p, hipStream_t s) {
   // us, with eight waves 33.7 us; 256 units of 1,100 rows 19.1 us, 15.5 us).
   // With two on a CU eight are no faster (512 units of 500 to 3,500 rows 54.5
   // us, 55.1 us).
-  const bool thin = sizeof(T) * D == 128 && static_cast<int64_t>(units) * p.splits <= p.cus;
+  const bool thin = sizeof(T) * D == 128 && static_cast<int64_t>(units) * p.even_splits <= p.cus;
   // Wider rows, one split each: a CU's only workgroup bounds the call where
   // other CUs have none, or shorter ones, and streams faster with eight waves
   // (192 units of 600 to 4,800 rows: four waves 59.8 us, eight 55.3 us; 144 even
@@ -661,7 +724,9 @@ hipError_t launch_typed(const DecodeParams &p, hipStream_t s) {
   // of 1,100 rows: four 24.1 us, eight 25.2 us; of 4,800: 92.0 us, 94.6 us; ragged
   // ones of 600 to 4,800: 68.2 us, 65.0 us).
   const bool alone = p.splits == 1 && 8 * static_cast<int64_t>(units) <= 7 * static_cast<int64_t>(p.cus);
-  if (kEight && (p.splits >= kWideMinSplits || thin || alone) && tiles_cap >= 6 * p.splits)
+  // Where uneven units may take more splits, two workgroups of four waves share a
+  // CU; two of eight do so only at 128 bytes a row.
+  if (kEight && (p.even_splits >= kWideMinSplits || thin || alone) && tiles_cap >= 6 * p.splits)
     hipLaunchKernelGGL((decode_split_kernel<T, D, kEight ? 8 : 4>), dim3(p.splits, units),
                        dim3((kEight ? 8 : 4) * kWave), 0, s, p);
   else

@@ -22,7 +22,9 @@ struct DecodeParams {
   float *part_o;          // [units][splits][group][D]
   float *part_ml;         // [units][splits][2][group]  (maxima, sums)
   int32_t *dev_err;
-  int layer0, n_layers, batch, hkv, cap, group, hq, splits;
+  int layer0, n_layers, batch, hkv, cap, group, hq;
+  int splits;             // launched per unit, and the partials' layout
+  int even_splits;        // taken per unit where the units are long and even: splits, or fewer but at least 2
   int cus;                // compute units of the device
   float scale_log2;       // logit scale * log2(e)
 };

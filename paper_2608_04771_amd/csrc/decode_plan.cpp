@@ -32,17 +32,17 @@ size_t partial_bytes(int units, int splits, int head_dim) {
 }
 }  // namespace
 
-int decode_call_splits(int splits, int units, int capacity, int group, int head_dim, int compute_units) {
-  const int tiles_cap = (capacity + 1 + kDecodeTile - 1) / kDecodeTile;
-  if (splits == 1 || units > compute_units || tiles_cap < 160 * splits) return splits;
+int decode_launch_splits(int splits, int units, int capacity, int group, int head_dim, int elem_bytes,
+                         int compute_units) {
+  if (splits != 2 || units > compute_units || units > kDecodeHeldUnits) return splits;
   int more = 2 * compute_units / units;
   const int fit = splits * (16 * head_dim + 32) / (group * (head_dim + 2));
-  const int most = tiles_cap / 64;
   if (more > fit) more = fit;
-  if (more > most) more = most;
-  if (more > kDecodeMaxSplits) more = kDecodeMaxSplits;
-  if (2 * units * more < 3 * compute_units) return splits;
-  return more > splits ? more : splits;
+  const int tiles_cap = (capacity + 1 + kDecodeTile - 1) / kDecodeTile;
+  if (more < 4 || tiles_cap < 320 || 2 * more * units < 3 * compute_units) return splits;
+  const int row_bytes = head_dim * elem_bytes;
+  if ((row_bytes == 128 || row_bytes == 512) && 5 * units * splits > 4 * compute_units) return splits;
+  return more;
 }
 
 size_t decode_workspace_bytes(int units, int capacity, int head_dim, int compute_units) {

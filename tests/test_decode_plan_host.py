@@ -1,27 +1,56 @@
 """The decode split rule on the host: a call never takes more partials than the
-memory sized for it holds, and never fewer splits than that size stands for."""
+memory sized for it holds, and never other splits than that size stands
+for but where more can pay.  The rule's source is compiled here
+with a C interface of its own, without the kernels."""
+import ctypes
 import itertools
+import os
+import shutil
+import subprocess
 
 import pytest
 
-from paper_2608_04771_amd import binding as B
+from paper_2608_04771_amd.build import CSRC
+
+SHIM = """
+#include "decode_plan.hpp"
+extern "C" int sized(int units, int cap, int cus) { return reco::decode_splits(units, cap, cus); }
+extern "C" int launched(int splits, int units, int cap, int group, int dim, int elem, int cus) {
+  return reco::decode_launch_splits(splits, units, cap, group, dim, elem, cus);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if cxx is None:
+        pytest.skip("no C++ compiler")
+    d = tmp_path_factory.mktemp("plan")
+    (d / "shim.cpp").write_text(SHIM)
+    so = str(d / "plan.so")
+    subprocess.run([cxx, "-std=c++17", "-O1", "-shared", "-fPIC", f"-I{CSRC}", str(d / "shim.cpp"),
+                    os.path.join(CSRC, "decode_plan.cpp"), "-o", so], check=True)
+    return ctypes.CDLL(so)
 
 
 @pytest.mark.parametrize("cus", [1, 32, 64, 256, 304])
-@pytest.mark.parametrize("dim", [64, 128])
-def test_partials_fit_and_splits_stay_in_range(cus, dim):
-    lib = B.load_library()
-    base_of = lib._ZN4reco13decode_splitsEiii
-    call_of = lib._ZN4reco18decode_call_splitsEiiiiii
+@pytest.mark.parametrize("dim,elem", [(64, 2), (64, 4), (128, 2), (128, 4)])
+def test_partials_fit_and_splits_stay_in_range(plan, cus, dim, elem):
     caps = [1, 31, 255, 256, 4095, 5120, 9709, 10240, 16640, 32832, 65600, 1 << 20]
-    units = sorted({1, 2, 3, 4, 7, 16, 31, 32, 96, 112, 127, 128, 129, 200, 255, 256, 257, 512, 65535, cus, cus + 1})
+    units = sorted({1, 2, 3, 4, 7, 16, 31, 32, 96, 112, 127, 128, 129, 152, 200, 255, 256, 257, 512, 65535, cus, cus + 1,
+                    max(1, 3 * cus // 8), max(1, cus // 2)})
+    raised = 0
     for u, cap, group in itertools.product(units, caps, range(1, 17)):
-        base = base_of(u, cap, cus)
-        s = call_of(base, u, cap, group, dim, cus)
-        assert base <= s <= 128, (u, cap, group)
+        base = plan.sized(u, cap, cus)
+        assert 1 <= base <= 128, (u, cap, group)
+        s = plan.launched(base, u, cap, group, dim, elem, cus)
         # group x D outputs and 2 x group statistics a split, in the room of 16 x D + 32 a sized split
         assert s * group * (dim + 2) <= base * (16 * dim + 32), (u, cap, group)
-        if base == 1:                # one kernel, whatever the capacity: more splits would add a merge launch
-            assert s == 1, (u, cap, group)
-        if s > base:
-            assert u * s <= 2 * cus and (cap + 32) // 32 >= 64 * s and 2 * u * s >= 3 * cus, (u, cap, group)
+        if s != base:
+            raised += 1
+            # a merge there is anyway, lengths that a wave holds, 1.5 to 2 workgroups a compute unit, long enough
+            assert base == 2 and s in (4, 5) and u <= 128 and 3 * cus <= 2 * u * s <= 4 * cus, (u, cap, group)
+            assert (cap + 32) // 32 >= 320, (u, cap, group)
+            assert dim * elem == 256 or 5 * u * base <= 4 * cus, (u, cap, group)
+    assert raised > 0 or cus == 1

@@ -267,8 +267,12 @@ reco_status_t decode_common(const reco_kv_cache_t *cache, int32_t layer0, int32_
   if (G > 16) return RECO_ERR_UNSUPPORTED;
   const int units = n_layers * cache->batch * cache->n_kv_heads;
   const int cus = current_compute_units();
+  const int even_splits = use_scratch ? reco::decode_scratch_splits(units, cache->capacity, cache->head_dim, cus)
+                                      : reco::decode_splits(units, cache->capacity, cus);
+  const int splits = reco::decode_launch_splits(even_splits, units, cache->capacity, G, cache->head_dim,
+                                                cache->dtype == RECO_F32 ? 4 : 2, cus);
   if (use_scratch) {
-    if (reco::decode_scratch_bytes(units, cache->capacity, cache->head_dim, cus) > reco::kDecodeScratchBytes)
+    if (reco::decode_partials_bytes(units, splits, G, cache->head_dim) > reco::kDecodeScratchBytes)
       return RECO_ERR_WORKSPACE;
     if (reco::decode_scratch(&ws) != hipSuccess) return RECO_ERR_HIP;
   } else {
@@ -286,10 +290,8 @@ reco_status_t decode_common(const reco_kv_cache_t *cache, int32_t layer0, int32_
   p.out = out;
   p.lse = lse;
   p.row_stats = row_stats;
-  p.even_splits = use_scratch ? reco::decode_scratch_splits(units, cache->capacity, cache->head_dim, cus)
-                              : reco::decode_splits(units, cache->capacity, cus);
-  p.splits = reco::decode_launch_splits(p.even_splits, units, cache->capacity, G, cache->head_dim,
-                                        cache->dtype == RECO_F32 ? 4 : 2, cus);
+  p.even_splits = even_splits;
+  p.splits = splits;
   p.cus = cus;
   p.part_o = reinterpret_cast<float *>(ws);
   p.part_ml = p.part_o + static_cast<size_t>(units) * p.splits * G * cache->head_dim;

@@ -57,10 +57,9 @@ int decode_scratch_splits(int units, int capacity, int head_dim, int compute_uni
   return splits;
 }
 
-size_t decode_scratch_bytes(int units, int capacity, int head_dim, int compute_units) {
-  const int splits = decode_scratch_splits(units, capacity, head_dim, compute_units);
-  if (splits == 1) return 0;   // finalised in place, no partials
-  return partial_bytes(units, splits, head_dim);
+size_t decode_partials_bytes(int units, int splits, int group, int head_dim) {
+  if (splits == 1) return 0;
+  return static_cast<size_t>(units) * splits * group * (static_cast<size_t>(head_dim) + 2) * sizeof(float);
 }
 
 }  // namespace reco

@@ -54,8 +54,8 @@ constexpr size_t kDecodeScratchBytes = size_t(8) << 20;
 // with more units than compute units whose partials would not fit the array
 // takes one split per unit.
 int decode_scratch_splits(int units, int capacity, int head_dim, int compute_units);
-// Bytes of the array one call uses (0 when every unit is a single split,
-// which needs no partials).
-size_t decode_scratch_bytes(int units, int capacity, int head_dim, int compute_units);
+// Bytes of partials that a call of `splits` launched splits per unit writes (0
+// for one, which is finalised in place).
+size_t decode_partials_bytes(int units, int splits, int group, int head_dim);
 
 }  // namespace reco

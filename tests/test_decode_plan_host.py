@@ -18,6 +18,16 @@ extern "C" int sized(int units, int cap, int cus) { return reco::decode_splits(u
 extern "C" int launched(int splits, int units, int cap, int group, int dim, int elem, int cus) {
   return reco::decode_launch_splits(splits, units, cap, group, dim, elem, cus);
 }
+extern "C" int sized_static(int units, int cap, int dim, int cus) {
+  return reco::decode_scratch_splits(units, cap, dim, cus);
+}
+extern "C" size_t written(int units, int splits, int group, int dim) {
+  return reco::decode_partials_bytes(units, splits, group, dim);
+}
+extern "C" size_t static_bytes() { return reco::kDecodeScratchBytes; }
+extern "C" size_t workspace(int units, int cap, int dim, int cus) {
+  return reco::decode_workspace_bytes(units, cap, dim, cus);
+}
 """
 
 
@@ -31,7 +41,10 @@ def plan(tmp_path_factory):
     so = str(d / "plan.so")
     subprocess.run([cxx, "-std=c++17", "-O1", "-shared", "-fPIC", f"-I{CSRC}", str(d / "shim.cpp"),
                     os.path.join(CSRC, "decode_plan.cpp"), "-o", so], check=True)
-    return ctypes.CDLL(so)
+    lib = ctypes.CDLL(so)
+    for f in (lib.written, lib.static_bytes, lib.workspace):
+        f.restype = ctypes.c_size_t
+    return lib
 
 
 @pytest.mark.parametrize("cus", [1, 32, 64, 256, 304])
@@ -47,6 +60,13 @@ def test_partials_fit_and_splits_stay_in_range(plan, cus, dim, elem):
         s = plan.launched(base, u, cap, group, dim, elem, cus)
         # group x D outputs and 2 x group statistics a split, in the room of 16 x D + 32 a sized split
         assert s * group * (dim + 2) <= base * (16 * dim + 32), (u, cap, group)
+        assert plan.written(u, s, group, dim) == (0 if s == 1 else u * s * group * (dim + 2) * 4)
+        assert plan.written(u, s, group, dim) <= plan.workspace(u, cap, dim, cus), (u, cap, group)
+        # the static array of allocation-free calls: what they launch fits it, and what they write is what is checked
+        b = plan.sized_static(u, cap, dim, cus)
+        t = plan.launched(b, u, cap, group, dim, elem, cus)
+        assert b in (base, 1) and (t == s or b == 1), (u, cap, group)
+        assert plan.written(u, t, group, dim) <= plan.static_bytes(), (u, cap, group)
         if s != base:
             raised += 1
             # a merge there is anyway, lengths that a wave holds, 1.5 to 2 workgroups a compute unit, long enough

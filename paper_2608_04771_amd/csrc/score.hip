@@ -537,20 +537,20 @@ __device__ __forceinline__ void stats_groups(const ScoreParams &p, const Segment
       }
       if (next >= 0) load_keys<T, D>(kf, src, next);
     } else {
-      float m, z[4];
+      float m, z[4], a;
       int lim;
       unsigned far = 0;                            // row tiles to do again
       const auto begin = [&](int rt) {
         m = mref[rt * kTileRows + l32];
+        a = acc[rt * kTileRows];
         z[0] = z[1] = z[2] = z[3] = 0.f;
       };
       const auto arg = [&](float x) { return fmaf(x, c, -m); };
       const auto end_tile = [&](int rt) {
         const float sum = half_sum((z[0] + z[1]) + (z[2] + z[3]));
-        if (__any(!(sum <= kFarSum)))
-          far |= 1u << rt;
-        else
-          acc[rt * kTileRows] += sum;
+        const bool again = __any(!(sum <= kFarSum));
+        far |= again ? 1u << rt : 0u;
+        acc[rt * kTileRows] = a + (again ? 0.f : sum);
       };
       if (g0 + C::group <= end) {
         walk_rows<T, D>(kf, src, next, qrow, rt0, rw, tiles, begin, arg,
@@ -712,9 +712,9 @@ __device__ __forceinline__ float2 row_norm(const ScoreParams &p, const Segment &
     // M is a reference, and log2 Z an upper bound of how far above it the row's
     // largest logit lies.  Where that is far, M is raised to near it, by a whole
     // number, so that the exponents of the heavy keys are small in the mass pass.
-    const int e = (__double2hiint(Z) >> 20) - (1023 + kNearLog2);
-    const float m = M + static_cast<float>(max(e, 0));
-    n = make_float2(m, static_cast<float>(1.0 / ldexp(Z, -static_cast<int>(m - M))));
+    const float inv = static_cast<float>(1.0 / Z);
+    const float m = M + static_cast<float>(max(126 - kNearLog2 - static_cast<int>(__float_as_uint(inv) >> 23), 0));
+    n = make_float2(m, __builtin_amdgcn_ldexpf(inv, static_cast<int>(m - M)));
   }
   return n;
 }

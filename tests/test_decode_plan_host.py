@@ -51,8 +51,8 @@ def plan(tmp_path_factory):
 @pytest.mark.parametrize("dim,elem", [(64, 2), (64, 4), (128, 2), (128, 4)])
 def test_partials_fit_and_splits_stay_in_range(plan, cus, dim, elem):
     caps = [1, 31, 255, 256, 4095, 5120, 9709, 10240, 16640, 32832, 65600, 1 << 20]
-    units = sorted({1, 2, 3, 4, 7, 16, 31, 32, 96, 112, 127, 128, 129, 152, 200, 255, 256, 257, 512, 65535, cus, cus + 1,
-                    max(1, 3 * cus // 8), max(1, cus // 2)})
+    units = sorted({1, 2, 3, 4, 7, 16, 31, 32, 96, 112, 127, 128, 129, 152, 200, 255, 256, 257, 512, 65535, cus,
+                    cus + 1, max(1, 3 * cus // 8), max(1, cus // 2)})
     raised = 0
     for u, cap, group in itertools.product(units, caps, range(1, 17)):
         base = plan.sized(u, cap, cus)

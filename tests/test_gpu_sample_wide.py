@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_2608_04771_amd import binding as B
 from paper_2608_04771_amd import inputs as I
 
@@ -48,7 +49,7 @@ def test_draws_equal_those_of_small_calls(vocab, ld, T, base):
     ref, _ = _draw(zs, vocab, ids, reward[:few], T)
     assert tok[:few].tolist() == ref.tolist()
     assert z[:few].cpu().numpy().tobytes() == zs.cpu().numpy().tobytes()
-    # every other row: the penalty touches its ids alone, and the token is in range
+    # every other row: the penalty touches its ids alone, and the token is in range (and below, the oracle's)
     beta = torch.where(reward <= 0.4, 0.0, torch.where(reward >= 0.8, 3.0, 1.0))[:, None]
     want = z0.clone()
     want[:, ids.long()] = want[:, ids.long()] - beta
@@ -57,3 +58,22 @@ def test_draws_equal_those_of_small_calls(vocab, ld, T, base):
     if T == 0.0:
         finite = torch.nan_to_num(z[few:, :vocab], nan=-float("inf"))
         assert torch.equal(tok[few:].long(), finite.argmax(1))
+
+
+@pytest.mark.parametrize("rows,vocab,T", [(2112, 4096, 1.0), (683, 8191, 0.6), (300, 32000, 2.5)])
+def test_every_row_draws_the_oracles_token(rows, vocab, T):
+    """Every row of a call of many chunks (the rows above compare 16): the oracle's token, or one whose value is
+    within what two float32 logarithms of another library's rounding can move it."""
+    z = I.make_logits(rows, vocab, 21, device="cuda")
+    ids = torch.from_numpy(I.make_reflection_ids(64, vocab, 3)).cuda()
+    reward = torch.rand(rows, generator=torch.Generator().manual_seed(2)).cuda()
+    z0 = z.cpu().numpy()
+    tok, err = _draw(z, vocab, ids, reward, T)
+    assert err == 0
+    zp, ref, vals = oracle.penalty_sample(z0, ids.cpu().numpy(), reward.cpu().numpy(), 0.4, 0.8, 0.0, 1.0, 3.0, T,
+                                          77, 5)
+    assert z.cpu().numpy().tobytes() == zp.astype(np.float32).tobytes()
+    got = tok.cpu().numpy().astype(np.int64)
+    top, mine = vals[np.arange(rows), ref], vals[np.arange(rows), got]
+    assert np.all(mine >= top - 1e-5 * np.maximum(1.0, np.abs(top)))
+    assert np.mean(got == ref) > 0.99

@@ -18,8 +18,8 @@ namespace {
 // length) and row offsets then stay far inside int32.
 constexpr int32_t kMaxVocab = 1 << 30;
 
-// Largest capacity the score kernels take: their grid spans 8 x chunks
-// workgroups of 256 threads along x, which must stay below 2^32 work-items.
+// Largest capacity the score kernels take: positions rounded up to a chunk, and
+// the least partials of a call (a slot for every 512 keys), stay far inside int32.
 constexpr int32_t kMaxScoreCapacity = 1 << 29;
 
 bool cache_ok(const reco_kv_cache_t *c) {

@@ -2,8 +2,9 @@
 //
 // One "unit" is a (layer, sequence, kv head) with n valid cache rows and G
 // query heads.  The grid is (splits, units): workgroup (s, u) walks a
-// contiguous range of 32-key tiles of unit u with its four waves interleaved
-// over the tiles, so the workgroup streams one contiguous stretch of K and V.
+// contiguous range of 32-key tiles of unit u with its waves (four, or eight
+// where a CU holds one workgroup that bounds the call) interleaved over the
+// tiles, so the workgroup streams one contiguous stretch of K and V.
 //
 // Per 32-key tile a wave computes, on the matrix cores,
 //   S^T = K_tile . Q^T            (M = 16 keys per half, N = 16 padded queries)
@@ -25,14 +26,13 @@
 // split partial: every store and load of that merge is 16 bytes on a row pitch
 // free of bank conflicts (as 4-byte stores on a pitch of D, 16 lanes on one
 // bank, it took 2 us of each call: 28 one-layer calls 397 -> 359 us, 256 units
-// x 1,100 rows 27.8 -> 26.5 us, 112 units x 9,645 rows 88.2 -> 86.4 us).  A second kernel
-// merges the splits of each unit, writes out / lse and commits the optional
-// append (so no workgroup of the attention kernel races on len); a unit
-// covered by a single workgroup (one split) is finalised by that workgroup,
-// with no second launch.  Merging in
-// the last-finishing workgroup instead would need device-scope fences, which
-// on this chip write back and invalidate the L2 that the streaming
-// workgroups depend on.
+// x 1,100 rows 27.8 -> 26.5 us, 112 units x 9,645 rows 88.2 -> 86.4 us).  A
+// second kernel merges the splits of each unit, writes out / lse and commits the
+// optional append (so no workgroup of the attention kernel races on len); a unit
+// covered by a single workgroup (one split) is finalised by that workgroup, with
+// no second launch.  Merging in the last-finishing workgroup instead would need
+// device-scope fences, which on this chip write back and invalidate the L2 that
+// the streaming workgroups depend on.
 #include "reco_device.hpp"
 #include "decode_attn.hpp"
 #include "decode_plan.hpp"
@@ -73,8 +73,8 @@ struct DecodeCfg {
   static constexpr int lanes_per_row = row_bytes / 16;
   static constexpr int rows_per_inst = kWave / lanes_per_row;
   static constexpr int v_insts = kTile / rows_per_inst;
-  // Two workgroups per CU (two waves per SIMD) where the double-buffered
-  // tile fits in 256 registers; the fp32 head_dim-128 variant needs more.
+  // Two workgroups of four waves per CU (two waves per SIMD) where a tile and the
+  // outputs fit in 256 registers; the fp32 head_dim-128 variant needs more.
   static constexpr int min_wgs = (sizeof(T) == 4 && D == 128) || NW == 8 ? 1 : 2;
 };
 
@@ -702,17 +702,17 @@ hipError_t launch_typed(const DecodeParams &p, hipStream_t s) {
   const int units = p.n_layers * p.batch * p.hkv;
   // Eight waves where a split holds more tiles than four waves take in one
   // round and nothing else hides the second round: small calls of long units
-  // (28 one-layer calls of 4 units x 9,645 rows: 352 us against 359 us).  With
-  // few splits per unit (longer runs of tiles) eight waves only add to the
-  // merge (112 units x 9,645 rows: 88.4 us against 86.4 us).
+  // (28 one-layer calls of 4 units x 9,645 rows: four waves 359 us, eight 352 us).
+  // With few splits per unit (longer runs of tiles) eight waves only add to the
+  // merge (112 units x 9,645 rows: four 86.4 us, eight 88.4 us).
   const int tiles_cap = (p.cap + 1 + kTile - 1) / kTile;
   // fp32 at head_dim 128 needs more than the 256 registers that eight waves
   // leave a lane (808 bytes of scratch).
   constexpr bool kEight = !(sizeof(T) == 4 && D == 128);
   // Rows of 128 bytes make tiles of half the size: with one workgroup on a CU
-  // four waves have too little on its way (200 units of 600 to 4,500 rows 50.6
-  // us, with eight waves 33.7 us; 256 units of 1,100 rows 19.1 us, 15.5 us).
-  // With two on a CU eight are no faster (512 units of 500 to 3,500 rows 54.5
+  // four waves have too little on their way (200 units of 600 to 4,500 rows: four
+  // waves 50.6 us, eight 33.7 us; 256 units of 1,100 rows: 19.1 us, 15.5 us).
+  // With two on a CU eight are no faster (512 units of 500 to 3,500 rows: 54.5
   // us, 55.1 us).
   const bool thin = sizeof(T) * D == 128 && static_cast<int64_t>(units) * p.even_splits <= p.cus;
   // Wider rows, one split each: a CU's only workgroup bounds the call where
@@ -724,8 +724,8 @@ hipError_t launch_typed(const DecodeParams &p, hipStream_t s) {
   // of 1,100 rows: four 24.1 us, eight 25.2 us; of 4,800: 92.0 us, 94.6 us; ragged
   // ones of 600 to 4,800: 68.2 us, 65.0 us).
   const bool alone = p.splits == 1 && 8 * static_cast<int64_t>(units) <= 7 * static_cast<int64_t>(p.cus);
-  // Where uneven units may take more splits, two workgroups of four waves share a
-  // CU; two of eight do so only at 128 bytes a row.
+  // (Where uneven units may take more than two splits, two workgroups of four
+  // waves share a CU; two of eight do so only at 128 bytes a row.)
   if (kEight && (p.even_splits >= kWideMinSplits || thin || alone) && tiles_cap >= 6 * p.splits)
     hipLaunchKernelGGL((decode_split_kernel<T, D, kEight ? 8 : 4>), dim3(p.splits, units),
                        dim3((kEight ? 8 : 4) * kWave), 0, s, p);

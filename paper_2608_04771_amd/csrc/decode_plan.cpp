@@ -4,16 +4,16 @@
 
 namespace reco {
 
-// Splits per unit: at most one workgroup per compute unit of the device
-// (256 on a whole MI355X, fewer on a partition of it).  Measured on the
-// 7B-shaped cache, a single resident round with one workgroup per CU streams
-// fastest: two workgroups sharing a CU finish later than the rest, and a
-// second round adds its ramp to the tail.  At least four 32-key tiles per
-// split at capacity.  With more units than compute units the grid runs in
-// several rounds anyway; there long units (8K rows or more at capacity) are
-// cut in two, which halves the work of the last workgroups to finish (the
-// ragged 7B batch: 4.49 -> 4.27 ms per call; the 32B 64K batch 12.03 ->
-// 11.91 ms).
+// Splits per unit that the workspace is sized for, and that a call takes unless
+// decode_launch_splits adds to them: at most one workgroup per compute unit of
+// the device (256 on a whole MI355X, fewer on a partition of it).  With even
+// units a single resident round with one workgroup per CU streams fastest: two
+// workgroups sharing a CU finish later than the rest, and a second round adds its
+// ramp to the tail.  At least four 32-key tiles per split at capacity.  With more
+// units than compute units the grid runs in several rounds anyway; there long
+// units (8K rows or more at capacity) are cut in two, which halves the work of the
+// last workgroups to finish (the ragged 7B batch: 4.49 -> 4.27 ms per call; the
+// 32B 64K batch 12.03 -> 11.91 ms).
 int decode_splits(int units, int capacity, int compute_units) {
   const int tiles_cap = (capacity + 1 + kDecodeTile - 1) / kDecodeTile;
   int splits = compute_units / units;

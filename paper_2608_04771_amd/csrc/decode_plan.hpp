@@ -12,7 +12,8 @@ constexpr int kDecodeTile = 32;          // keys per wave iteration of the atten
 constexpr int kDecodeMaxSplits = 128;    // most splits the merge kernels take
 constexpr int kDecodeHeldUnits = 128;    // units whose lengths a wave holds
 
-// compute_units: CUs of the device the call runs on (sets the split count).
+// Splits per unit that the workspace is sized for; compute_units: CUs of the
+// device the call runs on.
 int decode_splits(int units, int capacity, int compute_units);
 // The splits a call launches per unit, `splits` being those that its partials'
 // memory is sized for: that size counts 16 query rows a split, a call writes

@@ -107,14 +107,6 @@ __device__ __forceinline__ float group4_sum(float v) {
   v += shfl_xor(v, 32);
   return v;
 }
-// Reduce over the 16 lanes of one lane group (lanes 16g .. 16g+15).
-__device__ __forceinline__ float row16_sum(float v) {
-  v += shfl_xor(v, 1);
-  v += shfl_xor(v, 2);
-  v += shfl_xor(v, 4);
-  v += shfl_xor(v, 8);
-  return v;
-}
 
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll

@@ -66,7 +66,7 @@ struct ScoreCfg {
   static constexpr int KT = pieces <= 8 ? 2 : 1;        // 32-key tiles per wave group (64 K registers either way)
   static constexpr int group = 32 * KT;                 // keys per wave group
   static constexpr int q_stride = row_bytes + 16;       // LDS pitch of a window row: eight rows cover all banks
-  // Row tiles staged at once: the rows, the per-wave sums and the reference must fit the LDS of a CU.
+  // Row tiles staged at once: the rows, the per-wave sums and the references must fit the LDS of a CU.
   static constexpr int max_tiles = row_bytes == 128 ? 28 : row_bytes == 256 ? 16 : 8;
   static constexpr int max_rows = max_tiles * kTileRows;
   static constexpr int q_bytes = max_rows * q_stride;
@@ -74,7 +74,8 @@ struct ScoreCfg {
   static constexpr int stats_lds = q_bytes + sum_bytes + max_rows * 4;
   static constexpr int mass_lds = q_bytes + max_rows * 8;
   static constexpr int lost_keys = 4096;                // longest mass segment of a call with several row blocks
-  static_assert(stats_lds <= 160 * 1024 && mass_lds + lost_keys * 4 + kWaves * kWave * 4 + 16 <= 160 * 1024, "window rows and statistics fit one CU's LDS");
+  static_assert(stats_lds <= 160 * 1024 && mass_lds + lost_keys * 4 + kWaves * kWave * 4 + 16 <= 160 * 1024,
+                "window rows and statistics fit one CU's LDS");
 };
 
 // ---------------------------------------------------------------------------

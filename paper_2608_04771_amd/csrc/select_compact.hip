@@ -10,11 +10,15 @@
 //   one scan over the waves' counts and ballots within a wave then give every
 //   kept position (entries above theta, plus the first `need` entries equal to
 //   theta) its place in ascending order, and the window positions come after
-//   them.  A workgroup has a CU to itself and is bound by its chain of passes:
-//   up to kHeld scores a thread stay in registers instead of being read four
-//   times, each bin is counted in four copies (scores crowd into few bins of
-//   the first pass), and a bin is found by all threads (112 units of 16,384:
-//   the whole call, 229 us of it compaction, 264 -> 247 us).
+//   them.  A workgroup is bound by its chain of passes: up to kHeld scores a
+//   thread stay in registers instead of being read four times, each bin is
+//   counted in four copies (scores crowd into few bins of the first pass), and a
+//   bin is found by all threads (112 units of 16,384: the whole call, 229 us of
+//   it compaction, 264 -> 247 us).  With more units than CUs two workgroups share
+//   a CU, if their waves' scalar registers fit a SIMD: of more than 80 (and the
+//   trap handler's 16) not eight do (512 units of 1,000 rows: with 94 40.3 us, with
+//   80 36.6 us; 2,048 of 200 85.6 us, 66.3 us; 512 of 30,000 936 us, 881 us; what
+//   is spilled to keep to 80 takes 0.3 us of the smaller calls).
 // compact: one 256-thread workgroup per (unit, K or V, 128-byte column slice)
 //   moves row idx[p] to row p for p = 0..m-1 in ascending chunks of 256
 //   rows.  Because idx is strictly increasing, idx[p] >= p: a chunk's sources
@@ -36,6 +40,7 @@ constexpr int kSelWaves = kSelThreads / kWave;
 constexpr int kHeld = 16;                    // scores a thread keeps in registers
 constexpr int kCopies = 4;                   // copies of each histogram bin
 constexpr int kMaxBins = 2048;
+constexpr int kSelSgprs = 80;                // two workgroups on a CU
 constexpr int kCompThreads = 256;
 constexpr int kSliceBytes = 128;             // row slice per compaction workgroup
 constexpr int kLanesPerRow = kSliceBytes / 16;
@@ -60,7 +65,7 @@ __device__ __forceinline__ uint32_t score_bits(float s, bool *bad) {
   return u;
 }
 
-__global__ __launch_bounds__(kSelThreads) void select_kernel(SelectParams p) {
+__global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_num_sgpr(kSelSgprs))) void select_kernel(SelectParams p) {
   __shared__ __attribute__((aligned(16))) int hist[kMaxBins * kCopies];
   __shared__ int wsum[kSelWaves];
   __shared__ int2 wcount[kSelWaves];

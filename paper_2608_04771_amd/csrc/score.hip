@@ -565,7 +565,8 @@ __device__ __forceinline__ void stats_groups(const ScoreParams &p, const Segment
             },
             arg, [&](int kt, int i, float e) { z[i & 3] += tile_key(kt * 32, i, 0) <= lim ? e : 0.f; }, end_tile);
       }
-      if (far != 0) {                              // their keys again, then the next group's
+      // Out of the way of the loop (small calls run its code cold: 0.5 us of 16 us).
+      if (__builtin_expect(far != 0, 0)) {         // their keys again, then the next group's
         load_keys<T, D>(kf, src, g0);
         for (; far != 0; far &= far - 1)
           far_tile<T, D>(p, seg, kf, qrow, mref, acc, r0, __ffs(far) - 1, g0, l32, half);

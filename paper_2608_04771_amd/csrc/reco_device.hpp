@@ -119,6 +119,27 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
+// v of another lane of the same 16, by the vector unit alone (a shuffle goes
+// through the LDS unit, some 100 cycles each).
+constexpr int kDppXor1 = 0xb1, kDppXor2 = 0x4e, kDppMirror = 0x140, kDppHalfMirror = 0x141;
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, 0xf, 0xf, true));
+}
+
+// f over all 64 lanes, in every lane: quads, eights, sixteens, halves, all.
+template <typename F>
+__device__ __forceinline__ float wave_fold(float v, F f) {
+  v = f(v, dpp<kDppXor1>(v));
+  v = f(v, dpp<kDppXor2>(v));
+  v = f(v, dpp<kDppHalfMirror>(v));
+  v = f(v, dpp<kDppMirror>(v));
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = f(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return f(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
 // Record a device precondition failure: the first code wins.
 __device__ __forceinline__ void report(int32_t *dev_err, int32_t code) {
   if (dev_err) atomicCAS(dev_err, 0, code);

@@ -721,11 +721,6 @@ __device__ __forceinline__ float2 row_norm(const ScoreParams &p, const Segment &
   return n;
 }
 
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, 0xf, 0xf, true));
-}
-
 // Sum over the 32 lanes of each half, of the 16 * KT registers of a group:
 // each step halves the registers and folds one bit of the register index into
 // the lane index, so the lane ends with the total of one key (KT = 2), or the
@@ -734,7 +729,7 @@ __device__ __forceinline__ float dpp(float v) {
 // summed over later).
 template <int KT>
 __device__ __forceinline__ float fold_keys(float (&a)[KT * 16], int lane) {
-  constexpr int kRor8 = 0x128, kHalfMirror = 0x141, kXor2 = 0x4e, kXor1 = 0xb1;
+  constexpr int kRor8 = 0x128;
   float b[16];
   if constexpr (KT == 2) {
 #pragma unroll
@@ -757,15 +752,15 @@ __device__ __forceinline__ float fold_keys(float (&a)[KT * 16], int lane) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {                  // register bit 2 <-> lane bit 2
     const float own = (lane & 4) ? b[4 + i] : b[i], other = (lane & 4) ? b[i] : b[4 + i];
-    b[i] = own + dpp<kHalfMirror>(other);
+    b[i] = own + dpp<kDppHalfMirror>(other);
   }
 #pragma unroll
   for (int i = 0; i < 2; ++i) {                  // register bit 1 <-> lane bit 1
     const float own = (lane & 2) ? b[2 + i] : b[i], other = (lane & 2) ? b[i] : b[2 + i];
-    b[i] = own + dpp<kXor2>(other);
+    b[i] = own + dpp<kDppXor2>(other);
   }
   const float own = (lane & 1) ? b[1] : b[0], other = (lane & 1) ? b[0] : b[1];
-  return own + dpp<kXor1>(other);
+  return own + dpp<kDppXor1>(other);
 }
 
 // Key of the group that fold_keys leaves in `lane`.

@@ -197,7 +197,11 @@ struct HeldLengths {
   }
 };
 
-template <typename T, int D, int NW>
+// HELD: the call may launch more splits than long even units take, and the
+// workgroups decide.  A form of its own, as its code in front of the others'
+// start costs them up to 1% (256 units of 1,100 rows: with it 23.22 us, without
+// 23.06 us; two fp32 units of 2,048 at head_dim 64: 8.71 us, 8.62 us).
+template <typename T, int D, int NW, bool HELD>
 __global__ __launch_bounds__(NW * kWave, (DecodeCfg<T, D, NW>::min_wgs)) void decode_split_kernel(DecodeParams p) {
   using Cfg = DecodeCfg<T, D, NW>;
   constexpr int kThreads = NW * kWave;
@@ -213,7 +217,7 @@ __global__ __launch_bounds__(NW * kWave, (DecodeCfg<T, D, NW>::min_wgs)) void de
   int split = blockIdx.x, unit = blockIdx.y;
   int active = p.splits;                           // splits that share the unit
   int len_in = 0;
-  if (p.splits > p.even_splits) {
+  if constexpr (HELD) {
     // Every workgroup finds the same from the same lengths (no one changes them
     // before the merge kernel: even_splits is 2 or more).  Its own unit's is one
     // of them; a load of its own would come after the decision.
@@ -249,7 +253,7 @@ __global__ __launch_bounds__(NW * kWave, (DecodeCfg<T, D, NW>::min_wgs)) void de
   const size_t cunit = (static_cast<size_t>(p.layer0 + lc) * p.batch + b) * p.hkv + h;
   const size_t qunit = static_cast<size_t>(lc) * per_layer + static_cast<size_t>(b) * p.hkv + h;
 
-  if (p.splits == p.even_splits) len_in = p.len[cunit];
+  if constexpr (!HELD) len_in = p.len[cunit];
   const int n_cache = len_in < 0 ? 0 : (len_in > p.cap ? p.cap : len_in);
   const bool append = p.k_new != nullptr;
   const int n_tot = n_cache + (append ? 1 : 0);
@@ -716,7 +720,7 @@ hipError_t launch_typed(const DecodeParams &p, hipStream_t s) {
   // waves 50.6 us, eight 33.7 us; 256 units of 1,100 rows: 19.1 us, 15.5 us).
   // With two on a CU eight are no faster (512 units of 500 to 3,500 rows: 54.5
   // us, 55.1 us).
-  const bool thin = sizeof(T) * D == 128 && static_cast<int64_t>(units) * p.even_splits <= p.cus;
+  const bool thin = sizeof(T) * D == 128 && static_cast<int64_t>(units) * p.splits <= p.cus;
   // Wider rows, one split each: a CU's only workgroup bounds the call where
   // other CUs have none, or shorter ones, and streams faster with eight waves
   // (192 units of 600 to 4,800 rows: four waves 59.8 us, eight 55.3 us; 144 even
@@ -728,11 +732,14 @@ hipError_t launch_typed(const DecodeParams &p, hipStream_t s) {
   const bool alone = p.splits == 1 && 8 * static_cast<int64_t>(units) <= 7 * static_cast<int64_t>(p.cus);
   // (Where uneven units may take more than two splits, two workgroups of four
   // waves share a CU; two of eight do so only at 128 bytes a row.)
-  if (kEight && (p.even_splits >= kWideMinSplits || thin || alone) && tiles_cap >= 6 * p.splits)
-    hipLaunchKernelGGL((decode_split_kernel<T, D, kEight ? 8 : 4>), dim3(p.splits, units),
-                       dim3((kEight ? 8 : 4) * kWave), 0, s, p);
+  constexpr int kHeldWaves = sizeof(T) * D == 128 ? 8 : 4;
+  const dim3 grid(p.splits, units);
+  if (p.splits > p.even_splits)
+    hipLaunchKernelGGL((decode_split_kernel<T, D, kHeldWaves, true>), grid, dim3(kHeldWaves * kWave), 0, s, p);
+  else if (kEight && (p.splits >= kWideMinSplits || thin || alone) && tiles_cap >= 6 * p.splits)
+    hipLaunchKernelGGL((decode_split_kernel<T, D, kEight ? 8 : 4, false>), grid, dim3((kEight ? 8 : 4) * kWave), 0, s, p);
   else
-    hipLaunchKernelGGL((decode_split_kernel<T, D, 4>), dim3(p.splits, units), dim3(4 * kWave), 0, s, p);
+    hipLaunchKernelGGL((decode_split_kernel<T, D, 4, false>), grid, dim3(4 * kWave), 0, s, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.splits == 1) return e;   // one split: finalised in place
   if (p.splits >= kWideMinSplits)

@@ -37,6 +37,11 @@ def _inputs(units, G, dtype, D, lens, cap):
     return B.KVCache(k, v, n), q, kn, vn
 
 
+def _nans(cache, G):
+    """A workspace of NaNs: what a call reads of it has to come from the call."""
+    return B.decode_workspace(cache, G).fill_(0xff)
+
+
 @pytest.mark.parametrize("kind", ["even", "short", "one long", "ragged"])
 @pytest.mark.parametrize("units,G,dtype,D", [(128, 7, "bf16", 128), (96, 4, "bf16", 128), (97, 4, "f32", 64),
                                              (96, 3, "bf16", 64), (100, 2, "f32", 128)])
@@ -45,7 +50,7 @@ def test_units_of_any_lengths(units, G, dtype, D, kind):
     cache, q, kn, vn = _inputs(units, G, dtype, D, lens, CAP)
     other, _, _, _ = _inputs(units, G, dtype, D, lens, CAP)
     stats = torch.empty((1, units, G, 2), dtype=torch.float32, device="cuda")
-    out, lse = B.reco_decode_attn(cache, q, kn, vn, row_stats=stats)
+    out, lse = B.reco_decode_attn(cache, q, kn, vn, ws=_nans(cache, G), row_stats=stats)
     for u, n in enumerate(lens):
         kk = torch.cat([other.k[0, u, 0, :n], kn[0, u]]).double()
         vv = torch.cat([other.v[0, u, 0, :n], vn[0, u]]).double()
@@ -68,6 +73,6 @@ def test_long_even_units_take_two_splits(units, G, dtype, D):
     lens = [9000 + 100 * (u % 9) for u in range(units)]
     cache, q, kn, vn = _inputs(units, G, dtype, D, lens, CAP)
     less, _, _, _ = _inputs(units, G, dtype, D, lens, CAP - 300)
-    out, lse = B.reco_decode_attn(cache, q, kn, vn)
+    out, lse = B.reco_decode_attn(cache, q, kn, vn, ws=_nans(cache, G))
     ref, ref_lse = B.reco_decode_attn(less, q, kn, vn)
     assert torch.equal(out, ref) and torch.equal(lse, ref_lse)

@@ -32,17 +32,18 @@
 // with perfect overlap: an MFMA takes about 10 cycles of its SIMD's issue.
 //
 // Measured (both sides in turn): 28 layers x 4 heads x 16,384 keys, 448
-// rows, two passes: 442 us, after 534 us with 16x16x32 tiles in turn with
-// their exponentials and a row-merge kernel between the passes.  Under that
-// load the card lowers its clock (1.4 GHz against 2.1 GHz in short runs), so
-// it is the energy of the products that bounds the call, and variants with
-// fewer stalls measure the same.  64 units of 65,536 keys, 160 rows, one pass:
-// 247 us (4.4 TB/s of K) after 255 us.  Two fp32 units of 2,048 keys: 27 us
-// after 98 us (their keys and row tiles spread over 66 CUs instead of 8).
-// Slower: the next group's K fragments held in registers a group ahead (they
-// spill: 309 us for the 64 units, where reloading each fragment after its last
-// use takes 245 us), and touching the next group's lines a group ahead (275 us:
-// the fragments' 16-byte accesses keep the address unit busy half of the time).
+// rows, two passes: 538 us with 16x16x32 tiles in turn with their exponentials
+// and a row-merge kernel between the passes, now 448 us.  Counters there: the
+// VALU issues in 60 to 62% of the cycles, the matrix core is busy in 45 to 47%,
+// one or the other in 78 to 80%, so what the two waves of a SIMD do not overlap
+// bounds the call.  64 units of 65,536 keys, 160 rows, one pass: 254 us, now
+// 249 us (4.3 TB/s of K): there the pipes work in 64% of the cycles and the
+// address unit in 56%, as the fragments' 16-byte accesses take 32 bytes of each
+// row, with few products to hide behind.  Two fp32 units of 2,048 keys: 97.7 us,
+// now 26.8 us (their keys and row tiles spread over 66 CUs instead of 8).
+// Slower for the 64 units: the next group's K fragments held in registers a
+// group ahead (they spill: 309 us, where reloading each fragment after its last
+// use took 245 us), and touching the next group's lines a group ahead (275 us).
 #include "reco_device.hpp"
 #include "reco_kernels.hpp"
 

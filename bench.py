@@ -66,12 +66,12 @@ DECODE_TRAFFIC = {
     "sources": ("paper_2608_04771_amd/csrc/decode_attn.hip", "paper_2608_04771_amd/csrc/reco_device.hpp",
                 "paper_2608_04771_amd/csrc/decode_attn.hpp", "paper_2608_04771_amd/csrc/decode_plan.hpp",
                 "paper_2608_04771_amd/csrc/decode_plan.cpp"),
-    "sha256": "6b4f18c40baea51e63b07fc4ad16c9a5ce20cf66a3001f6d2f2c27fb0e51fdc6",
+    "sha256": "6f5621f8be0e0d0b5a1072ba218b44bb632b4d3071bc0329420aaa06e70434ad",
     # (fetched, written) bytes per decode_split_kernel dispatch, mean over a timed step's calls
     "per_workload": {
-        "7b-28L-28q4kv-d128-bf16-L16384": (553563105, 838908),
-        "7b-28L-28q4kv-d128-bf16-B32-L4k-32k": (27334648150, 26263581),
-        "32b-64L-40q8kv-d128-bf16-B8-L65536": (78250524791, 21495849),
+        "7b-28L-28q4kv-d128-bf16-L16384": (553619391, 839007),
+        "7b-28L-28q4kv-d128-bf16-B32-L4k-32k": (27337430979, 26263584),
+        "32b-64L-40q8kv-d128-bf16-B8-L65536": (78258500053, 21495848),
     },
 }
 

@@ -555,14 +555,14 @@ __global__ __launch_bounds__(kWave) void decode_merge_kernel(DecodeParams p) {
   for (int s = 0; s < kPre; ++s) {
     const float wgt = __shfl(w0, s, kWave);       // -1 for s >= S
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) acc[i] += wgt < 0.f ? 0.f : wgt * pre[s][i];
+    for (int i = 0; i < kPer; ++i) acc[i] = fmaf(wgt, wgt < 0.f ? 0.f : pre[s][i], acc[i]);
   }
   for (int s = kPre; s < S; ++s) {
     const float wgt = __shfl(s < kWave ? w0 : w1, s & (kWave - 1), kWave);
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
       const float x = po[static_cast<size_t>(s) * G * D + lane + i * kWave];
-      acc[i] += wgt < 0.f ? 0.f : wgt * x;
+      acc[i] = fmaf(wgt, wgt < 0.f ? 0.f : x, acc[i]);
     }
   }
   T *out = reinterpret_cast<T *>(p.out) + ((static_cast<size_t>(lc) * p.batch + b) * p.hq + h * p.group + qi) * D;
